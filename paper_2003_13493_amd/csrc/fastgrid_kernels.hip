@@ -600,15 +600,25 @@ __device__ int collect(const uint8_t *smem, const Seg &s0, const Seg &s1, const 
 }
 
 // Entries of this lane's compass rounds when at least four waves share the
-// sub-tile (at most four rounds: MAX_GROUPS <= 4 * 256).
+// sub-tile (at most four rounds: MAX_GROUPS <= 4 * 256); rounds past the last
+// group are left out (uniform).
 __device__ __forceinline__ void group_cache_fill(GroupCache &c, const Seg &s0, const Seg &s1, const Seg &s2) {
     const int lane = lane_id(), wave = threadIdx.x >> 6, stride = (blockDim.x >> 6) * 64;
     const GroupSeq q = group_seq(s0, s1, s2);
     const int i = wave * 64 + lane;
-    c.e01 = group_entry(s0, s1, s2, q, i) | (group_entry(s0, s1, s2, q, i + stride) << 16);
-    c.e23 = group_entry(s0, s1, s2, q, i + 2 * stride) | (group_entry(s0, s1, s2, q, i + 3 * stride) << 16);
+    c.e23 = NO_GROUP | (NO_GROUP << 16);
+    c.e01 = group_entry(s0, s1, s2, q, i) | (NO_GROUP << 16);
+    if (q.total > stride) c.e01 = (c.e01 & 0xFFFFu) | (group_entry(s0, s1, s2, q, i + stride) << 16);
+    if (q.total > 2 * stride)
+        c.e23 = group_entry(s0, s1, s2, q, i + 2 * stride) | (group_entry(s0, s1, s2, q, i + 3 * stride) << 16);
 }
 static_assert(MAX_GROUPS <= 4 * 256, "four compass rounds per wave with four or more waves");
+
+__device__ __forceinline__ void group_cache_fill(GroupCache &c, const Geo &g0, const Geo &g1, const Geo &g2,
+                                                 int nl) {
+    group_cache_fill(c, make_seg(g0, has_area(g0)), make_seg(g1, nl > 1 && has_area(g1)),
+                     make_seg(g2, nl > 2 && has_area(g2)));
+}
 
 // P3: keep entries that pass the 8-point test, compacted in place.  A lane
 // past the end reads a stale slot (the list has a spare slot per lane beyond
@@ -709,10 +719,11 @@ struct NoHook {
 //
 // `cache` (workgroups of four or more waves only) keeps the compass group
 // entries across calls whose staged geometry has the same `cache_key`
-// (-1: recompute).
+// (-1: recompute; FILLED: the caller has filled it).
+constexpr int FILLED = -2;
 template <class Before = NoHook, class After = NoHook>
 __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Geo &g2, int nl,
-                           const Params &P, uint32_t *keys, GroupCache *cache = nullptr, int cache_key = -1,
+                           const Params &P, uint32_t *keys, GroupCache *cache = nullptr, int cache_key = FILLED,
                            Before before = Before(), After after = After()) {
     const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     uint8_t *scratch = smem + OFF_WAVES + wave * wave_bytes(nwaves);
@@ -721,14 +732,15 @@ __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Ge
     const Seg s0 = make_seg(g0, has_area(g0));
     const Seg s1 = make_seg(g1, nl > 1 && has_area(g1));
     const Seg s2 = make_seg(g2, nl > 2 && has_area(g2));
-    if (cache && (cache_key < 0 || __builtin_amdgcn_readfirstlane(cache->key) != cache_key)) {
+    if (cache && cache_key != FILLED &&
+        (cache_key < 0 || __builtin_amdgcn_readfirstlane(cache->key) != cache_key)) {
         group_cache_fill(*cache, s0, s1, s2);
         cache->key = cache_key;
     }
     const uint32_t ce01 = cache ? cache->e01 : 0u, ce23 = cache ? cache->e23 : 0u;
     // every level's groups start 4 bytes past a multiple of 8 (uniform): true
-    // for fused sub-tiles, whose origins are on the 16-pixel grid; the single
-    // deeper levels of process_subtile_upper may start elsewhere
+    // for fused sub-tiles, whose origins are on the 16-pixel grid; the levels
+    // of an upper region may start elsewhere
     const bool a8 = ((s0.tbase + s0.gc0) & 7) == 4 && (!s1.n || ((s1.tbase + s1.gc0) & 7) == 4) &&
                     (!s2.n || ((s2.tbase + s2.gc0) & 7) == 4);
     int n1 = 0;
@@ -1044,38 +1056,10 @@ __device__ void process_subtile(const fg_job &J, int sx0, int sy0, int xr1, int 
     run_passes(smem, g0, g1, g2, fused_levels(J), P, (uint32_t *)(smem + OFF_KEYS));
 }
 
-// Levels MAX_FUSED .. L-1 of one level-0 sub-tile (already built in their
-// planes): one level at a time, loaded with a 4-pixel halo.
-__device__ void process_subtile_upper(const fg_job &J, int sx0, int sy0, int xr1, int yr1,
-                                      const Params &P, uint8_t *smem) {
-    for (int k = MAX_FUSED; k < J.levels; ++k) {
-        Geo g;
-        level_area(J, k, sx0, sy0, xr1, yr1, g);
-        if (!has_area(g)) continue;
-        const int tx = (g.sx - 4) & ~15, ty = g.sy - 4;
-        const int tw = ((g.ex + 4 + 15) & ~15) - tx, th = g.ey + 4 - ty;
-        __syncthreads();
-        load_tile(smem + T0, J.lvl[k], g.H, J.pitch[k], tx, ty, tw, th);
-        zero_lds(smem + OFF_M0, (M0_ROWS * M0_P * 2 + 15) & ~15);
-        __syncthreads();
-        g.tbase = T0;
-        g.tx = tx;
-        g.ty = ty;
-        g.moff = OFF_M0;
-        g.mp = M0_P;
-        set_groups(g);
-        Params Pk = P;
-        if (P.smap[0]) {
-            Pk.smap[0] = J.smap[k];
-            Pk.spitch[0] = J.smap_pitch[k];
-        }
-        run_passes(smem, g, g, g, 1, Pk, (uint32_t *)(smem + OFF_KEYS));
-    }
-}
-
 // A region of a job: its cells and its level-0 extent.
 struct Region {
     int rxi, ryi;        // region column and row
+    int rcells;          // cells per region side
     int ncx, ncy;        // cells across and down (clipped at the grid edge)
     int xr1, yr1;        // level-0 end of the region (clipped at the image)
     Params P;
@@ -1085,6 +1069,7 @@ __device__ __forceinline__ Region region_of(const fg_job &J, int region) {
     Region R;
     R.ryi = region < (1 << 21) ? div_small(region, J.rx) : region / J.rx;
     R.rxi = region - R.ryi * J.rx;
+    R.rcells = J.rcells;
     R.ncx = min(J.rcells, J.gw - R.rxi * J.rcells);
     R.ncy = min(J.rcells, J.gh - R.ryi * J.rcells);
     R.P.t = J.t;
@@ -1112,7 +1097,7 @@ __device__ void keys_write(const fg_job &J, const Region &R, const uint32_t *key
                            int nthreads = blockDim.x) {
     for (int i = tid; i < R.ncx * R.ncy; i += nthreads) {
         const int qy = div_small(i, R.ncx);   // i < MAX_KEYS
-        const int cx = R.rxi * J.rcells + i - qy * R.ncx, cy = R.ryi * J.rcells + qy;
+        const int cx = R.rxi * R.rcells + i - qy * R.ncx, cy = R.ryi * R.rcells + qy;
         const uint32_t key = keys[i];
         // fast_feature {x, y, score, level, reserved} as one little-endian word
         uint64_t f;
@@ -1148,7 +1133,7 @@ __device__ void detect_region(const fg_job &J, int region, uint8_t *smem) {
 __device__ void keys_from_slots(const fg_job &J, const Region &R, uint32_t *keys) {
     for (int i = threadIdx.x; i < R.ncx * R.ncy; i += blockDim.x) {
         const int qy = div_small(i, R.ncx);
-        const int cx = R.rxi * J.rcells + i - qy * R.ncx, cy = R.ryi * J.rcells + qy;
+        const int cx = R.rxi * R.rcells + i - qy * R.ncx, cy = R.ryi * R.rcells + qy;
         const uint64_t f = gload<uint64_t>(J.out + (size_t)cy * J.gw + cx);
         const uint32_t score = (uint32_t)(f >> 32) & 0xFFFFu;
         uint32_t key = 0;
@@ -1161,19 +1146,6 @@ __device__ void keys_from_slots(const fg_job &J, const Region &R, uint32_t *keys
         }
         keys[i] = key;
     }
-}
-
-// Levels MAX_FUSED .. L-1 of a region, merged into the slots of levels below.
-__device__ void detect_region_upper(const fg_job &J, int region, uint8_t *smem) {
-    const Region R = region_of(J, region);
-    uint32_t *keys = (uint32_t *)(smem + OFF_KEYS);
-    __syncthreads();
-    keys_from_slots(J, R, keys);
-    for (int sy0 = R.P.ry0; sy0 < R.yr1; sy0 += SUB)
-        for (int sx0 = R.P.rx0; sx0 < R.xr1; sx0 += SUB)
-            process_subtile_upper(J, sx0, sy0, R.xr1, R.yr1, R.P, smem);
-    __syncthreads();
-    keys_write(J, R, keys);
 }
 
 // Threads that own a quad of a fused level-0 tile (at most 96 rows of 4).
@@ -1225,20 +1197,18 @@ __device__ __forceinline__ void store_piece(uint8_t *plane, int P, int y, int x,
     }
 }
 
-// Commit a quad-staged level-0 tile to LDS, build levels 1 and 2 of it into
-// LDS from registers, and write the sub-tile's own level-1 and level-2 pixels
-// to their planes.  A quad's rows past the tile (at most three, still inside
-// the 96 level-0 rows of the LDS tile) are committed too: nothing reads them,
-// and the level rows they feed lie past the level tiles.
-__device__ void quad_commit(uint8_t *smem, const TileRegs &R, const Stage &st, const fg_job &J, const Geo &g1,
-                            const Geo &g2) {
-    const int ch = threadIdx.x & 7, q = threadIdx.x >> 3;
-    if (ch >= (st.tw >> 4) || 4 * q >= st.th) return;
+// Commit the quad R (rows 4q .. 4q+3 of chunk column ch) of a level-B tile of
+// F levels to LDS, build levels B+1 and B+2 of it into LDS from registers, and
+// write the area's own pixels of those levels to their planes.  A quad's rows
+// past the tile (at most three, still inside the 96 rows of the LDS tile) are
+// committed too: nothing reads them, and the level rows they feed lie past the
+// level tiles.
+__device__ __forceinline__ void quad_commit(uint8_t *smem, const TileRegs &R, int q, int ch, const Stage &st,
+                                            const fg_job &J, int B, int F, const Geo &g1, const Geo &g2) {
     uint8_t *t0 = smem + T0 + 4 * q * LP + 16 * ch;
 #pragma unroll
     for (int j = 0; j < 4; ++j) *(u32x4 *)(t0 + j * LP) = R.v[j];
-    const int nl = fused_levels(J);
-    if (nl < 2) return;
+    if (F < 2) return;
     const u32x4 a = R.v[0], b = R.v[1], c = R.v[2], d = R.v[3];
     const uint32_t r0a = halve4(make_uint2(a.x, a.y), make_uint2(b.x, b.y));
     const uint32_t r0b = halve4(make_uint2(a.z, a.w), make_uint2(b.z, b.w));
@@ -1247,12 +1217,170 @@ __device__ void quad_commit(uint8_t *smem, const TileRegs &R, const Stage &st, c
     *(uint2 *)(smem + T1 + (2 * q) * LP + 8 * ch) = make_uint2(r0a, r0b);
     *(uint2 *)(smem + T1 + (2 * q + 1) * LP + 8 * ch) = make_uint2(r1a, r1b);
     const int x1 = (st.tx >> 1) + 8 * ch, y1 = (st.ty >> 1) + 2 * q;
-    store_piece(J.lvl[1], J.pitch[1], y1, x1, (uint64_t)r0b << 32 | r0a, 8, g1);
-    store_piece(J.lvl[1], J.pitch[1], y1 + 1, x1, (uint64_t)r1b << 32 | r1a, 8, g1);
-    if (nl < 3) return;
+    store_piece(J.lvl[B + 1], J.pitch[B + 1], y1, x1, (uint64_t)r0b << 32 | r0a, 8, g1);
+    store_piece(J.lvl[B + 1], J.pitch[B + 1], y1 + 1, x1, (uint64_t)r1b << 32 | r1a, 8, g1);
+    if (F < 3) return;
     const uint32_t l2 = halve4(make_uint2(r0a, r0b), make_uint2(r1a, r1b));
     *(uint32_t *)(smem + T2 + q * LP + 4 * ch) = l2;
-    store_piece(J.lvl[2], J.pitch[2], (st.ty >> 2) + q, (st.tx >> 2) + 4 * ch, l2, 4, g2);
+    store_piece(J.lvl[B + 2], J.pitch[B + 2], (st.ty >> 2) + q, (st.tx >> 2) + 4 * ch, l2, 4, g2);
+}
+
+// ---------------------------------------------------------------------------
+// Levels past the fused ones, three at a time: levels B .. B+F-1 (B a multiple
+// of MAX_FUSED, F <= MAX_FUSED) of an upper region, built from level B-1 and
+// detected by one workgroup, folded into the slots of the levels below.
+//
+// The levels are small (level 3 holds 1/64 of the pixels), so what bounds the
+// pass is one workgroup's chain of loads, halvings and passes, and the launch.
+// One launch in place of one per level and a detection by level-0 regions (8
+// pixels of level 3 a workgroup): 4096x2160, 5 levels, 10.3 us instead of 33;
+// 1920x1080, 4 levels, 7.9 instead of 8 to 10.
+
+// Copy a level's area from its LDS tile to the plane, in pieces of 4 pixels
+// from columns that are multiples of 4.
+__device__ void store_area(const uint8_t *tile, const Geo &g, uint8_t *img, int P) {
+    const int x0 = g.sx & ~3, wpr = (g.ex - x0 + 3) >> 2, h = g.ey - g.sy;
+    if (wpr <= 0 || h <= 0) return;
+    for (int i = threadIdx.x; i < wpr * h; i += blockDim.x) {
+        const int yy = div_small(i, wpr), y = g.sy + yy, x = x0 + 4 * (i - yy * wpr);
+        store_piece(img, P, y, x, *(const uint32_t *)(tile + (y - g.ty) * LP + (x - g.tx)), 4, g);
+    }
+}
+
+// Level-B tile of an upper region: task i halves two rows of 32 bytes of level
+// B-1 into the 16 pixels of chunk column i % nch of tile row i / nch, and
+// writes those of the area to the level-B plane.  One row a task: a wave
+// issues an instruction every four cycles here, with one wave per SIMD, so the
+// work is spread over every lane (four rows a thread took 10.5 us where one
+// took 8.8).  Rows outside the plane read zero
+// through the buffer's range check; like the columns past it (row padding or
+// the next row), they feed no pixel that is used.
+struct UpperRows {
+    u32x4 a0, a1, b0, b1;
+};
+
+__device__ __forceinline__ void upper_issue(UpperRows &u, const __amdgpu_buffer_rsrc_t &rs, int i, int tasks,
+                                            int nch, int sp, int y0, const Stage &st, const Geo &g) {
+    const int r = div_small(i, nch), gx = st.tx + 16 * (i - r * nch);
+    u.a0 = u.a1 = u.b0 = u.b1 = u32x4{0u, 0u, 0u, 0u};
+    if (i >= tasks || gx < 0 || gx >= g.W) return;
+    const int off = (st.ty + r - y0) * 2 * sp + 2 * gx;   // negative: out of range, reads zero
+    u.a0 = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+    u.a1 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0);
+    u.b0 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + sp, 0, 0);
+    u.b1 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + sp + 16, 0, 0);
+}
+
+__device__ __forceinline__ void upper_commit(const UpperRows &u, uint8_t *tile, const fg_job &J, int B, int i,
+                                             int tasks, int nch, const Stage &st, const Geo &g) {
+    if (i >= tasks) return;
+    const int r = div_small(i, nch), ch = i - r * nch;
+    u32x4 o;
+    o.x = halve4(make_uint2(u.a0.x, u.a0.y), make_uint2(u.b0.x, u.b0.y));
+    o.y = halve4(make_uint2(u.a0.z, u.a0.w), make_uint2(u.b0.z, u.b0.w));
+    o.z = halve4(make_uint2(u.a1.x, u.a1.y), make_uint2(u.b1.x, u.b1.y));
+    o.w = halve4(make_uint2(u.a1.z, u.a1.w), make_uint2(u.b1.z, u.b1.w));
+    *(u32x4 *)(tile + r * LP + 16 * ch) = o;
+    const int gx = st.tx + 16 * ch, gy = st.ty + r;
+    store_piece(J.lvl[B], J.pitch[B], gy, gx, (uint64_t)o.y << 32 | o.x, 8, g);
+    store_piece(J.lvl[B], J.pitch[B], gy, gx + 8, (uint64_t)o.w << 32 | o.z, 8, g);
+}
+
+// An upper region: `region` in the row-major grid of fg_upper_cells cells.
+__device__ Region upper_region_of(const fg_job &J, int region) {
+    Region R = region_of(J, 0);   // the parameters every region shares
+    const int rc = fg_upper_cells(J.cell, J.rcells), urx = (J.gw + rc - 1) / rc;
+    R.ryi = region / urx;
+    R.rxi = region - R.ryi * urx;
+    R.rcells = rc;
+    R.ncx = min(rc, J.gw - R.rxi * rc);
+    R.ncy = min(rc, J.gh - R.ryi * rc);
+    R.P.rx0 = R.rxi * rc * J.cell;
+    R.P.ry0 = R.ryi * rc * J.cell;
+    R.P.ncx = R.ncx;
+    R.xr1 = min(R.P.rx0 + R.ncx * J.cell, J.w[0]);
+    R.yr1 = min(R.P.ry0 + R.ncy * J.cell, J.h[0]);
+    return R;
+}
+
+// Area of level k of an upper region staged at `st` on level B.
+__device__ __forceinline__ void upper_geo(const fg_job &J, const Region &R, int k, int B, const Stage &st, Geo &g) {
+    g.k = k;
+    g.W = J.w[k];
+    g.H = J.h[k];
+    g.sx = R.P.rx0 >> k;
+    g.sy = R.P.ry0 >> k;
+    g.ex = min(R.xr1 >> k, g.W);
+    g.ey = min(R.yr1 >> k, g.H);
+    const int d = k - B;
+    g.tbase = sel3(d, T0, T1, T2);
+    g.tx = st.tx >> d;
+    g.ty = st.ty >> d;
+    g.moff = sel3(d, OFF_M0, OFF_M1, OFF_M2);
+    g.mp = MP;
+    set_groups(g);
+}
+
+// SCORES: write the score maps of the levels instead of selecting features.  B
+// is a template argument because a by-value job indexed by a variable is copied
+// to scratch memory (13 us instead of 7.9 for a 1920x1080 frame).
+template <int B, bool SCORES>
+__device__ __forceinline__ void upper_region(const fg_job &J, int region, uint8_t *smem) {
+    Region R = upper_region_of(J, region);
+    constexpr int TOP = B + MAX_FUSED <= FAST_MAX_LEVELS ? MAX_FUSED : FAST_MAX_LEVELS - B;   // levels there can be
+    const int F = min(J.levels - B, TOP);
+    const int sx = R.P.rx0 >> B, sy = R.P.ry0 >> B;
+    const int ex = min(R.xr1 >> B, J.w[B]), ey = min(R.yr1 >> B, J.h[B]);
+    if (ex <= sx || ey <= sy) return;   // no pixel of level B, so none above
+    const int H0 = 4 << (F - 1);
+    Stage st;
+    st.tx = (sx - H0) & ~15;
+    st.ty = (sy - H0) & ~3;   // the two levels above start on whole rows
+    st.tw = ((ex + H0 + 15) & ~15) - st.tx;
+    st.th = ey + H0 - st.ty;
+    Geo g0, g1, g2;
+    upper_geo(J, R, B, B, st, g0);
+    g1 = g0;
+    g2 = g0;
+    if (F > 1) upper_geo(J, R, B + 1, B, st, g1);
+    if constexpr (TOP > 2)
+        if (F > 2) upper_geo(J, R, B + 2, B, st, g2);
+    uint32_t *keys = (uint32_t *)(smem + OFF_KEYS);
+    const int nch = st.tw >> 4, tasks = nch * st.th, sp = J.pitch[B - 1];
+    const int y0 = max(st.ty, 0), y1 = min(st.ty + st.th, g0.H);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(J.lvl[B - 1] + (ptrdiff_t)(2 * y0) * sp), (short)0, max(y1 - y0, 0) * 2 * sp, 0x00020000);
+    UpperRows u;
+    upper_issue(u, rs, threadIdx.x, tasks, nch, sp, y0, st, g0);
+    // while the first rows load: the maps, the slots so far, the compass groups
+    zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
+    if (!SCORES) keys_from_slots(J, R, keys);
+    GroupCache cache;
+    const bool cached = blockDim.x >= 256;
+    if (cached) group_cache_fill(cache, g0, g1, g2, F);
+    for (int i = threadIdx.x;;) {
+        upper_commit(u, smem + T0, J, B, i, tasks, nch, st, g0);
+        i += blockDim.x;
+        if (i - (int)threadIdx.x >= tasks) break;   // uniform
+        upper_issue(u, rs, i, tasks, nch, sp, y0, st, g0);
+    }
+    __syncthreads();
+    if (F > 1) {
+        halve_two(smem + T0, smem + T1, smem + T2, st.tw, st.th, F > 2);
+        __syncthreads();
+        if (has_area(g1)) store_area(smem + T1, g1, J.lvl[B + 1], J.pitch[B + 1]);
+        if constexpr (TOP > 2)
+            if (F > 2 && has_area(g2)) store_area(smem + T2, g2, J.lvl[B + 2], J.pitch[B + 2]);
+    }
+    if (SCORES)
+        for (int l = 0; l < TOP; ++l) {   // entries past F are not used
+            R.P.smap[l] = J.smap[B + l];
+            R.P.spitch[l] = J.smap_pitch[B + l];
+        }
+    run_passes(smem, g0, g1, g2, F, R.P, keys, cached ? &cache : nullptr);
+    if (SCORES) return;
+    __syncthreads();
+    keys_write(J, R, keys);
 }
 
 // Issue the level-0 tile loads of a single-fused-sub-tile region.
@@ -1267,7 +1395,8 @@ __device__ __forceinline__ void region_commit(uint8_t *smem, const fg_job &J, in
     const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
     Geo g0, g1, g2;
     describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
-    quad_commit(smem, T, st, J, g1, g2);
+    const int ch = threadIdx.x & 7, q = threadIdx.x >> 3;
+    if (ch < (st.tw >> 4) && 4 * q < st.th) quad_commit(smem, T, q, ch, st, J, 0, fused_levels(J), g1, g2);
 }
 
 // Bijective block -> item map that gives each XCD (blocks are dealt to the 8
@@ -1289,15 +1418,6 @@ __device__ void scores_region(const fg_job &J, int region, uint8_t *smem) {
     }
     for (int sy0 = P.ry0; sy0 < R.yr1; sy0 += SUB)
         for (int sx0 = P.rx0; sx0 < R.xr1; sx0 += SUB) process_subtile(J, sx0, sy0, R.xr1, R.yr1, P, smem);
-}
-
-// Score-map mode of levels MAX_FUSED.. of a region.
-__device__ void scores_region_upper(const fg_job &J, int region, uint8_t *smem) {
-    const Region R = region_of(J, region);
-    Params P = R.P;
-    P.smap[0] = J.smap[MAX_FUSED];   // non-null selects the mode; each level sets its own
-    for (int sy0 = P.ry0; sy0 < R.yr1; sy0 += SUB)
-        for (int sx0 = P.rx0; sx0 < R.xr1; sx0 += SUB) process_subtile_upper(J, sx0, sy0, R.xr1, R.yr1, P, smem);
 }
 
 // Standalone NMS over (2r+1) x (2r+1) neighbourhoods and the cell arg-max
@@ -1373,14 +1493,20 @@ __global__ void __launch_bounds__(512) nms_grid_kernel(fg_job J, int radius) {
     keys_write(J, R, keys);
 }
 
+// The kernel arguments' cache lines, fetched together at a kernel's start.
+// They lie in host-visible memory and each costs a first access about 700
+// cycles; read where they are first used, they queue one behind the other
+// (3000 of the 12300 cycles of a 320x240 frame's workgroup, 1700 this way).
+__device__ __forceinline__ void touch_arguments() {
+    const auto p = (const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    static_assert(sizeof(fg_job) + 16 <= 384, "the argument and the block size lie in six lines");
+    const uint32_t a = p[0], b = p[16], c = p[32], d = p[48], e = p[64], f = p[80];
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+}
+
 __global__ void __launch_bounds__(512) score_plain_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     scores_region(J, xcd_item(blockIdx.x, gridDim.x), smem);
-}
-
-__global__ void __launch_bounds__(512) score_upper_plain_kernel(fg_job J) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    scores_region_upper(J, xcd_item(blockIdx.x, gridDim.x), smem);
 }
 
 __global__ void __launch_bounds__(512) detect_plain_kernel(fg_job J) {
@@ -1388,18 +1514,23 @@ __global__ void __launch_bounds__(512) detect_plain_kernel(fg_job J) {
     detect_region(J, xcd_item(blockIdx.x, gridDim.x), smem);
 }
 
-// Levels MAX_FUSED.. of one frame, one region per block.
-__global__ void __launch_bounds__(512) detect_upper_plain_kernel(fg_job J) {
+// Levels B .. B+2 of one frame, one upper region per block.
+template <int B, bool SCORES>
+__global__ void __launch_bounds__(512) upper_plain_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    detect_region_upper(J, xcd_item(blockIdx.x, gridDim.x), smem);
+    touch_arguments();
+    upper_region<B, SCORES>(J, blockIdx.x, smem);
 }
 
-// Levels MAX_FUSED.. of the batch's deep jobs, one listed region per block.
-__global__ void __launch_bounds__(512) detect_upper_batch_kernel(const fg_job *__restrict__ jobs,
-                                                                 const fg_item *__restrict__ items) {
+// Levels B .. B+2 of the batch's jobs that have them, one listed upper region
+// per block.
+template <int B>
+__global__ void __launch_bounds__(512) upper_batch_kernel(const fg_job *__restrict__ jobs,
+                                                          const fg_item *__restrict__ items) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const fg_item it = items[blockIdx.x];
-    detect_region_upper(jobs[it.job], (int)it.region, smem);
+    const fg_job &J = jobs[it.job];
+    if (J.levels > B) upper_region<B, false>(J, (int)it.region, smem);
 }
 
 // Persistent batched detectors.  Work items are regions of all jobs (items[]
@@ -1614,14 +1745,6 @@ __global__ void pyr_kernel(const uint8_t *__restrict__ src, int sp, uint8_t *__r
     pyr_row_words(src, sp, dst, dp, dw, y, w);
 }
 
-__global__ void pyr_batch_kernel(const fg_job *__restrict__ jobs, int k) {
-    const fg_job &J = jobs[blockIdx.z];
-    if (k >= J.levels || k < MAX_FUSED) return;
-    const int w = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
-    if (4 * w >= J.w[k] || y >= J.h[k]) return;
-    pyr_row_words(J.lvl[k - 1], J.pitch[k - 1], J.lvl[k], J.pitch[k], J.w[k], y, w);
-}
-
 }  // namespace
 
 void fg_job_layout(fg_job &j, const fg_launch &L) {
@@ -1652,38 +1775,29 @@ hipError_t fg_launch_pyramid(const fg_job &j, hipStream_t s) {
     return hipSuccess;
 }
 
+// The passes over levels MAX_FUSED.. of one frame, in order.
+static hipError_t launch_upper(const fg_job &j, const fg_launch &L, bool scores, hipStream_t s) {
+    const int n = fg_upper_regions(j);
+    if (j.levels > 3)
+        hipLaunchKernelGGL((scores ? upper_plain_kernel<3, true> : upper_plain_kernel<3, false>), dim3(n),
+                           dim3(L.block), fg_smem_bytes(L.block), s, j);
+    if (j.levels > 6)
+        hipLaunchKernelGGL((scores ? upper_plain_kernel<6, true> : upper_plain_kernel<6, false>), dim3(n),
+                           dim3(L.block), fg_smem_bytes(L.block), s, j);
+    return hipGetLastError();
+}
+
 hipError_t fg_launch_plain(const fg_job &j, const fg_launch &L, hipStream_t s) {
     hipLaunchKernelGGL(detect_plain_kernel, dim3(j.rx * j.ry), dim3(L.block),
                        fg_smem_bytes(L.block), s, j);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || j.levels <= MAX_FUSED) return e;
-    // deeper levels: built from the fused pass's last level, then detected
-    for (int k = MAX_FUSED; k < j.levels; ++k) {
-        dim3 grid(((j.w[k] + 3) / 4 + 63) / 64, j.h[k]);
-        hipLaunchKernelGGL(pyr_kernel, grid, dim3(64), 0, s, j.lvl[k - 1], j.pitch[k - 1], j.lvl[k],
-                           j.w[k], j.h[k], j.pitch[k]);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(detect_upper_plain_kernel, dim3(j.rx * j.ry), dim3(L.block),
-                       fg_smem_bytes(L.block), s, j);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_upper(j, L, false, s);
 }
 
 hipError_t fg_launch_score_maps(const fg_job &j, const fg_launch &L, hipStream_t s) {
     hipLaunchKernelGGL(score_plain_kernel, dim3(j.rx * j.ry), dim3(L.block), fg_smem_bytes(L.block), s, j);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || j.levels <= MAX_FUSED) return e;
-    for (int k = MAX_FUSED; k < j.levels; ++k) {
-        dim3 grid(((j.w[k] + 3) / 4 + 63) / 64, j.h[k]);
-        hipLaunchKernelGGL(pyr_kernel, grid, dim3(64), 0, s, j.lvl[k - 1], j.pitch[k - 1], j.lvl[k],
-                           j.w[k], j.h[k], j.pitch[k]);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(score_upper_plain_kernel, dim3(j.rx * j.ry), dim3(L.block), fg_smem_bytes(L.block),
-                       s, j);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_upper(j, L, true, s);
 }
 
 hipError_t fg_launch_nms_grid(const fg_job &j, int radius, hipStream_t s) {
@@ -1691,9 +1805,8 @@ hipError_t fg_launch_nms_grid(const fg_job &j, int radius, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int njobs, int total,
-                           int total_upper, int max_levels, int max_w1, int max_h1, bool all_single,
-                           unsigned *counter, const fg_launch &L, hipStream_t s) {
+hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int total, int total_upper,
+                           int max_levels, bool all_single, unsigned *counter, const fg_launch &L, hipStream_t s) {
     int blocks = L.num_cu * L.blocks_per_cu;
     if (blocks > total) blocks = total;
     if (blocks < 1) blocks = 1;
@@ -1703,19 +1816,12 @@ hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int njo
     else
         hipLaunchKernelGGL(detect_batch_generic_kernel, dim3(blocks), dim3(L.block), fg_smem_bytes(L.block), s,
                            jobs_dev, items, total, counter);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || total_upper == 0) return e;
-    int mw = max_w1, mh = max_h1;
-    for (int k = 2; k < max_levels; ++k) {
-        mw = (mw >> 1) > 0 ? (mw >> 1) : 1;
-        mh = (mh >> 1) > 0 ? (mh >> 1) : 1;
-        if (k < MAX_FUSED) continue;
-        dim3 grid(((mw + 3) / 4 + 63) / 64, mh, njobs);
-        hipLaunchKernelGGL(pyr_batch_kernel, grid, dim3(64), 0, s, jobs_dev, k);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(detect_upper_batch_kernel, dim3(total_upper), dim3(L.block), fg_smem_bytes(L.block),
-                       s, jobs_dev, items + total);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || max_levels <= MAX_FUSED) return e;
+    hipLaunchKernelGGL(upper_batch_kernel<3>, dim3(total_upper), dim3(L.block), fg_smem_bytes(L.block), s, jobs_dev,
+                       items + total);
+    if (max_levels > 2 * MAX_FUSED)
+        hipLaunchKernelGGL(upper_batch_kernel<6>, dim3(total_upper), dim3(L.block), fg_smem_bytes(L.block), s,
+                           jobs_dev, items + total);
     return hipGetLastError();
 }

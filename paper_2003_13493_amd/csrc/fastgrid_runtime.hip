@@ -43,6 +43,16 @@ struct TableSlot {
 
 constexpr size_t items_offset(int njobs) { return (sizeof(fg_job) * (size_t)njobs + 15) & ~(size_t)15; }
 
+// The work items of a batch: one per region of every job, then one per upper
+// region of every job with more than FG_MAX_FUSED levels.
+struct Work {
+    int total = 0, total_upper = 0, max_levels = 1;
+    int limited = 0;          // what fast_submit_static's limit counts: regions, twice for jobs past 3 levels
+    bool all_single = true;   // every job's regions are single sub-tiles
+
+    int items() const { return total + total_upper; }   // at most `limited`
+};
+
 struct Plan {
     bool live = false;
     fg_job *dev = nullptr;
@@ -51,8 +61,7 @@ struct Plan {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int njobs = 0;
-    int total = 0, total_upper = 0, max_levels = 0, mw1 = 0, mh1 = 0;
-    bool all_single = true;
+    Work work;
     bool launched = false;
     hipStream_t last_stream = nullptr;   // launches of a plan are ordered on one stream
 };
@@ -319,16 +328,10 @@ int ticket_state(fast_ctx *c, uint64_t tk) {
     return hip_fail(c, e, "hipEventQuery");
 }
 
-int build_table(fast_ctx *c, const fast_job *jobs, int njobs, fg_job *table, int &total, int &total_upper,
-                int &max_levels, int &max_w1, int &max_h1, bool &all_single) {
+int build_table(fast_ctx *c, const fast_job *jobs, int njobs, fg_job *table, Work &work) {
     if (!jobs) return fail(c, FAST_EINVAL, "jobs is NULL");
     if (njobs < 1 || njobs > FAST_MAX_JOBS) return fail(c, FAST_EINVAL, "njobs not in 1..4096");
-    total = 0;
-    total_upper = 0;
-    all_single = true;
-    max_levels = 1;
-    max_w1 = 1;
-    max_h1 = 1;
+    work = Work();
     for (int i = 0; i < njobs; ++i) {
         const fast_job &q = jobs[i];
         int rc = make_job(c, q.pyr, q.levels, q.t, q.n, q.cell, q.score, q.out, table[i]);
@@ -336,15 +339,13 @@ int build_table(fast_ctx *c, const fast_job *jobs, int njobs, fg_job *table, int
             c->err = "job " + std::to_string(i) + ": " + c->err;
             return rc;
         }
-        table[i].region_base = total;
-        total += table[i].rx * table[i].ry;
-        if (q.levels > FG_MAX_FUSED) total_upper += table[i].rx * table[i].ry;
-        if (table[i].rcells * table[i].cell > FG_SUB) all_single = false;
-        if (q.levels > max_levels) max_levels = q.levels;
-        if (q.levels > 1) {
-            if (table[i].w[1] > max_w1) max_w1 = table[i].w[1];
-            if (table[i].h[1] > max_h1) max_h1 = table[i].h[1];
-        }
+        const fg_job &j = table[i];
+        table[i].region_base = work.total;
+        work.total += j.rx * j.ry;
+        work.limited += j.rx * j.ry * (q.levels > FG_MAX_FUSED ? 2 : 1);
+        if (q.levels > FG_MAX_FUSED) work.total_upper += fg_upper_regions(j);
+        if (q.levels > work.max_levels) work.max_levels = q.levels;
+        if (j.rcells * j.cell > FG_SUB) work.all_single = false;
     }
     return FAST_OK;
 }
@@ -353,8 +354,8 @@ int build_table(fast_ctx *c, const fast_job *jobs, int njobs, fg_job *table, int
 // regions clipped at a frame's right or bottom edge last, each group in job
 // and region order: the cheap items end the queue, so the persistent
 // workgroups run out of work closer together.
-// The regions of the jobs with more than FG_MAX_FUSED levels follow, in job
-// and region order, for the pass over their deeper levels.
+// The upper regions of the jobs with more than FG_MAX_FUSED levels follow, in
+// job and region order, for the passes over their deeper levels.
 void fill_items(const fg_job *table, int njobs, fg_item *items) {
     int n = 0;
     for (int pass = 0; pass < 2; ++pass) {
@@ -368,9 +369,11 @@ void fill_items(const fg_job *table, int njobs, fg_item *items) {
             }
         }
     }
-    for (int j = 0; j < njobs; ++j)
-        if (table[j].levels > FG_MAX_FUSED)
-            for (int r = 0; r < table[j].rx * table[j].ry; ++r) items[n++] = fg_item{(uint32_t)j, (uint32_t)r};
+    for (int j = 0; j < njobs; ++j) {
+        const fg_job &J = table[j];
+        const int regions = J.levels > FG_MAX_FUSED ? fg_upper_regions(J) : 0;
+        for (int r = 0; r < regions; ++r) items[n++] = fg_item{(uint32_t)j, (uint32_t)r};
+    }
 }
 
 }  // namespace
@@ -739,12 +742,11 @@ FG_API int fast_submit(fast_ctx *c, const fast_job *jobs, int njobs, void *strea
     if (slot < 0) return fail(c, FAST_EBUSY, "all job tables are in flight");
     DeviceGuard g(c->device);
     TableSlot &S = c->slots[slot];
-    int total, total_upper, max_levels, mw1, mh1;
-    bool all_single;
+    Work work;
     // the staging buffer always has room for FAST_MAX_JOBS jobs
-    int rc = build_table(c, jobs, njobs, (fg_job *)S.host, total, total_upper, max_levels, mw1, mh1, all_single);
+    int rc = build_table(c, jobs, njobs, (fg_job *)S.host, work);
     if (rc) return rc;
-    const int nitems = total + total_upper;
+    const int nitems = work.items();
     const size_t off = items_offset(njobs), bytes = off + sizeof(fg_item) * (size_t)nitems;
     if (bytes > S.cap) {
         // the slot is idle (its last submission has finished), so nothing
@@ -772,8 +774,8 @@ FG_API int fast_submit(fast_ctx *c, const fast_job *jobs, int njobs, void *strea
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemcpyAsync(S.dev, S.host, bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(c, e, "job table upload");
-    e = fg_launch_batch(jobs_dev, items_dev, njobs, total, total_upper, max_levels, mw1, mh1, all_single,
-                        S.counter, c->launch, s);
+    e = fg_launch_batch(jobs_dev, items_dev, work.total, work.total_upper, work.max_levels,
+                        work.all_single, S.counter, c->launch, s);
     if (e != hipSuccess) return hip_fail(c, e, "batch launch");
     rc = record_ticket(c, s, ticket);
     if (rc) return rc;
@@ -797,14 +799,12 @@ FG_API int fast_submit_static(fast_ctx *c, const fast_job *jobs, int njobs, void
         c->static_pending = false;
     }
     uint8_t *host = c->static_host;
-    int total, total_upper, max_levels, mw1, mh1;
-    bool all_single;
-    int rc = build_table(c, jobs, njobs, (fg_job *)(host + STATIC_COUNTER_BYTES), total, total_upper, max_levels,
-                         mw1, mh1, all_single);
+    Work work;
+    int rc = build_table(c, jobs, njobs, (fg_job *)(host + STATIC_COUNTER_BYTES), work);
     if (rc) return rc;
-    const int nitems = total + total_upper;
-    if (nitems > FAST_STATIC_MAX_ITEMS)
-        return fail(c, FAST_EINVAL, "the jobs need " + std::to_string(nitems) + " work items, more than the " +
+    const int nitems = work.items();
+    if (work.limited > FAST_STATIC_MAX_ITEMS)
+        return fail(c, FAST_EINVAL, "the jobs need " + std::to_string(work.limited) + " work items, more than the " +
                                         std::to_string(FAST_STATIC_MAX_ITEMS) + " the static scratch holds");
     const size_t off = static_items_offset(njobs), bytes = off + sizeof(fg_item) * (size_t)nitems;
     // the queue counters travel with the table, so they start at zero whatever
@@ -818,8 +818,8 @@ FG_API int fast_submit_static(fast_ctx *c, const fast_job *jobs, int njobs, void
     e = hipEventRecord(c->static_copied, s);
     if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord (static staging)");
     c->static_pending = true;
-    e = fg_launch_batch((const fg_job *)(dev + STATIC_COUNTER_BYTES), (const fg_item *)(dev + off), njobs, total,
-                        total_upper, max_levels, mw1, mh1, all_single, (unsigned *)dev, c->launch, s);
+    e = fg_launch_batch((const fg_job *)(dev + STATIC_COUNTER_BYTES), (const fg_item *)(dev + off),
+                        work.total, work.total_upper, work.max_levels, work.all_single, (unsigned *)dev, c->launch, s);
     if (e != hipSuccess) return hip_fail(c, e, "batch launch (static)");
     if (!ticket) return FAST_OK;
     return record_ticket(c, s, ticket);
@@ -1261,25 +1261,19 @@ FG_API int fast_plan_create(fast_ctx *c, const fast_job *jobs, int njobs, int fl
     if (!plan_id) return fail(c, FAST_EINVAL, "plan_id is NULL");
     if (flags & ~FAST_PLAN_GRAPH) return fail(c, FAST_EINVAL, "unknown plan flags");
     std::vector<fg_job> table((size_t)(njobs > 0 ? njobs : 1));
-    int total, total_upper, max_levels, mw1, mh1;
-    bool all_single;
-    int rc = build_table(c, jobs, njobs, table.data(), total, total_upper, max_levels, mw1, mh1, all_single);
+    Work work;
+    int rc = build_table(c, jobs, njobs, table.data(), work);
     if (rc) return rc;
     DeviceGuard g(c->device);
     reap(c, false);   // a setup call: release what destroyed plans left behind
     Plan p;
     p.njobs = njobs;
-    p.total = total;
-    p.total_upper = total_upper;
-    p.all_single = all_single;
-    p.max_levels = max_levels;
-    p.mw1 = mw1;
-    p.mh1 = mh1;
-    std::vector<fg_item> items((size_t)(total + total_upper));
+    p.work = work;
+    std::vector<fg_item> items((size_t)work.items());
     fill_items(table.data(), njobs, items.data());
     hipError_t e = hipMalloc((void **)&p.dev, sizeof(fg_job) * njobs);
     if (e != hipSuccess) return hip_fail(c, e, "hipMalloc plan table");
-    e = hipMalloc((void **)&p.items, sizeof(fg_item) * (total + total_upper));
+    e = hipMalloc((void **)&p.items, sizeof(fg_item) * items.size());
     if (e != hipSuccess) { (void)hipFree(p.dev); return hip_fail(c, e, "hipMalloc plan item map"); }
     e = hipMalloc((void **)&p.counter, FG_COUNTER_WORDS * sizeof(unsigned));
     if (e != hipSuccess) {
@@ -1289,15 +1283,14 @@ FG_API int fast_plan_create(fast_ctx *c, const fast_job *jobs, int njobs, int fl
     }
     e = hipMemcpy(p.dev, table.data(), sizeof(fg_job) * njobs, hipMemcpyHostToDevice);
     if (e == hipSuccess)
-        e = hipMemcpy(p.items, items.data(), sizeof(fg_item) * (total + total_upper), hipMemcpyHostToDevice);
+        e = hipMemcpy(p.items, items.data(), sizeof(fg_item) * items.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(p.counter, 0, FG_COUNTER_WORDS * sizeof(unsigned));
     if (e == hipSuccess && (flags & FAST_PLAN_GRAPH)) {
         if (!c->capture_stream) e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            hipError_t le = fg_launch_batch(p.dev, p.items, njobs, total, total_upper, max_levels, mw1, mh1,
-                                            all_single, p.counter,
-                                            c->launch, c->capture_stream);
+            hipError_t le = fg_launch_batch(p.dev, p.items, work.total, work.total_upper, work.max_levels,
+                                            work.all_single, p.counter, c->launch, c->capture_stream);
             e = hipStreamEndCapture(c->capture_stream, &p.graph);
             if (le != hipSuccess) e = le;
         }
@@ -1326,9 +1319,8 @@ FG_API int fast_plan_launch(fast_ctx *c, int plan_id, void *stream, uint64_t *ti
     p.launched = true;
     p.last_stream = s;
     hipError_t e = p.exec ? hipGraphLaunch(p.exec, s)
-                          : fg_launch_batch(p.dev, p.items, p.njobs, p.total, p.total_upper, p.max_levels, p.mw1, p.mh1,
-                                            p.all_single,
-                                            p.counter, c->launch, s);
+                          : fg_launch_batch(p.dev, p.items, p.work.total, p.work.total_upper, p.work.max_levels,
+                                            p.work.all_single, p.counter, c->launch, s);
     if (e != hipSuccess) return hip_fail(c, e, p.exec ? "hipGraphLaunch" : "plan launch");
     if (!ticket) return FAST_OK;
     return record_ticket(c, s, ticket);

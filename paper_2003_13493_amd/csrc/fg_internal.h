@@ -110,20 +110,37 @@ struct fg_item {
     uint32_t region;
 };
 
-// Pyramid levels detected from one level-0 load; deeper levels take a second
-// pass.
+// Pyramid levels detected from one level-0 load; each FG_MAX_FUSED levels
+// further up take one more pass (levels 3-5, then 6-7).
 constexpr int FG_MAX_FUSED = 3;
 
-// Batched path: `jobs_dev` is a device copy of njobs jobs whose region_base
+// Cells per side of an upper region, the part of a frame one workgroup takes
+// in the passes over levels 3.. : 128 level-0 pixels (16 of level 3), at most
+// 16 cells, and never less than a region of the level-0 pass, so that a frame
+// has no more upper regions than regions.  Measured for levels 3.. of one
+// frame: 1920x1080, 4 levels, 7.9 us with 128 (135 workgroups) and 9.0 with
+// 256 (40 of 256 CUs busy); 4096x2160, 5 levels, 10.3 us with 128 and 9.4 with
+// 256; 64 or fewer spend a workgroup's whole chain of loads and passes on 64
+// pixels of level 3 (27 us for that frame's 2176 regions).
+constexpr int FG_UPPER_SIDE = 128;
+__host__ __device__ constexpr int fg_upper_cells(int cell, int rcells) {
+    const int c = FG_UPPER_SIDE / cell;
+    return c < rcells ? rcells : (c > 16 ? 16 : c);
+}
+__host__ __device__ constexpr int fg_upper_regions(const fg_job &j) {
+    const int c = fg_upper_cells(j.cell, j.rcells);
+    return ((j.gw + c - 1) / c) * ((j.gh + c - 1) / c);
+}
+
+// Batched path: `jobs_dev` is a device copy of the jobs, whose region_base
 // fields are prefix sums.  items[0 .. total) lists every region of every job
-// once, in any order; items[total .. total + total_upper) lists every region
-// of the jobs with more than FG_MAX_FUSED levels (their deeper levels).
+// once, in any order; items[total .. total + total_upper) lists every upper
+// region of the jobs with more than FG_MAX_FUSED levels.
 // all_single: every job's regions are single 64x64 sub-tiles (the pipelined
 // kernel applies).  `counter` holds FG_COUNTER_WORDS zero-initialised words
 // that the kernel re-arms itself on exit.
-hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int njobs, int total,
-                           int total_upper, int max_levels, int max_w1, int max_h1, bool all_single,
-                           unsigned *counter, const fg_launch &L, hipStream_t s);
+hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int total, int total_upper, int max_levels,
+                           bool all_single, unsigned *counter, const fg_launch &L, hipStream_t s);
 
 // Regions of at most this side (level-0 pixels) are one fused sub-tile.
 constexpr int FG_SUB = 64;
