@@ -1504,6 +1504,53 @@ __device__ __forceinline__ void touch_arguments() {
     asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
 }
 
+// One frame whose regions are single fused sub-tiles, workgroups of at least
+// 256 threads: one region per block, staged as the pipelined kernel stages
+// (quad_issue, quad_commit), with everything that does not need the pixels
+// done while they load.  One wave per SIMD runs on a small frame, so the time
+// is the chain of one workgroup, not the throughput: barriers and LDS round
+// trips count, and a wave's instructions one by one (four cycles each).
+// `scores`: write score maps instead of selecting features.
+template <bool SCORES>
+__device__ __forceinline__ void single_region(const fg_job &J, uint8_t *smem) {
+    touch_arguments();
+    Region R = region_of(J, xcd_item(blockIdx.x, gridDim.x));
+    const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
+    TileRegs T;
+    quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], st);
+    uint32_t *keys = (uint32_t *)(smem + OFF_KEYS);
+    zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
+    if (!SCORES) keys_clear(keys, R.ncx * R.ncy);
+    const int nl = fused_levels(J);
+    Geo g0, g1, g2;
+    describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
+    GroupCache cache;
+    group_cache_fill(cache, g0, g1, g2, nl);
+    if (SCORES) {
+        for (int l = 0; l < MAX_FUSED; ++l) {
+            R.P.smap[l] = J.smap[l < J.levels ? l : 0];
+            R.P.spitch[l] = J.smap_pitch[l < J.levels ? l : 0];
+        }
+    }
+    const int ch = threadIdx.x & 7, q = threadIdx.x >> 3;
+    if (ch < (st.tw >> 4) && 4 * q < st.th) quad_commit(smem, T, q, ch, st, J, 0, nl, g1, g2);
+    __syncthreads();
+    run_passes(smem, g0, g1, g2, nl, R.P, keys, &cache);
+    if (SCORES) return;
+    __syncthreads();
+    keys_write(J, R, keys);
+}
+
+__global__ void __launch_bounds__(512) detect_single_kernel(fg_job J) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    single_region<false>(J, smem);
+}
+
+__global__ void __launch_bounds__(512) score_single_kernel(fg_job J) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    single_region<true>(J, smem);
+}
+
 __global__ void __launch_bounds__(512) score_plain_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     scores_region(J, xcd_item(blockIdx.x, gridDim.x), smem);
@@ -1787,15 +1834,19 @@ static hipError_t launch_upper(const fg_job &j, const fg_launch &L, bool scores,
     return hipGetLastError();
 }
 
+// Whether every region of the frame is one fused sub-tile that one workgroup
+// can stage at once (24 quads of 8 threads).
+static bool single_regions(const fg_job &j, const fg_launch &L) { return j.rcells * j.cell <= SUB && L.block >= 256; }
+
 hipError_t fg_launch_plain(const fg_job &j, const fg_launch &L, hipStream_t s) {
-    hipLaunchKernelGGL(detect_plain_kernel, dim3(j.rx * j.ry), dim3(L.block),
+    hipLaunchKernelGGL(single_regions(j, L) ? detect_single_kernel : detect_plain_kernel, dim3(j.rx * j.ry), dim3(L.block),
                        fg_smem_bytes(L.block), s, j);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_upper(j, L, false, s);
 }
 
 hipError_t fg_launch_score_maps(const fg_job &j, const fg_launch &L, hipStream_t s) {
-    hipLaunchKernelGGL(score_plain_kernel, dim3(j.rx * j.ry), dim3(L.block), fg_smem_bytes(L.block), s, j);
+    hipLaunchKernelGGL(single_regions(j, L) ? score_single_kernel : score_plain_kernel, dim3(j.rx * j.ry), dim3(L.block), fg_smem_bytes(L.block), s, j);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_upper(j, L, true, s);
 }
