@@ -1424,79 +1424,6 @@ __device__ void scores_region(const fg_job &J, int region, uint8_t *smem) {
         for (int sx0 = P.rx0; sx0 < R.xr1; sx0 += SUB) process_subtile(J, sx0, sy0, R.xr1, R.yr1, P, smem);
 }
 
-// Standalone NMS over (2r+1) x (2r+1) neighbourhoods and the cell arg-max
-// across levels, from global score maps (J.smap).  One workgroup per region;
-// each level's part of the region is walked in 64 x 64 tiles staged in LDS
-// with an r-pixel halo (zero outside the map).  Every tile pixel gets the
-// rank (score << 16) | (0xFFFF - its row-major index in the tile) (0 for
-// score 0): ranks are unique, and a higher rank means a higher score or, on
-// a tie, an earlier pixel, so a pixel survives exactly when its rank is the
-// maximum of its window.  The window maximum is separable: a row pass, then
-// a column pass, 2(2r+1) comparisons per pixel.
-constexpr int NMS_TILE = SUB + 2 * 4;
-constexpr int NMS_HMAX_OFF = NMS_TILE * NMS_TILE * 4;
-constexpr int NMS_KEYS_OFF = NMS_HMAX_OFF + NMS_TILE * SUB * 4;
-size_t nms_smem_bytes() { return (size_t)NMS_KEYS_OFF + MAX_KEYS * 4; }
-
-__global__ void __launch_bounds__(512) nms_grid_kernel(fg_job J, int radius) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int region = xcd_item(blockIdx.x, gridDim.x);
-    const Region R = region_of(J, region);
-    uint32_t *rank = (uint32_t *)smem;
-    uint32_t *hmax = (uint32_t *)(smem + NMS_HMAX_OFF);
-    uint32_t *keys = (uint32_t *)(smem + NMS_KEYS_OFF);
-    keys_clear(keys, R.ncx * R.ncy);
-    const int r = radius;
-    for (int k = 0; k < J.levels; ++k) {
-        const int x0 = R.P.rx0 >> k, y0 = R.P.ry0 >> k;
-        const int x1 = min(R.xr1 >> k, J.w[k]), y1 = min(R.yr1 >> k, J.h[k]);
-        const int cw = J.cell >> k;
-        const uint16_t *map = J.smap[k];
-        const int mp = J.smap_pitch[k];
-        for (int ty0 = y0; ty0 < y1; ty0 += SUB) {
-            for (int tx0 = x0; tx0 < x1; tx0 += SUB) {
-                const int tw = min(SUB, x1 - tx0), th = min(SUB, y1 - ty0);
-                const int TW = tw + 2 * r, TH = th + 2 * r;
-                __syncthreads();   // the previous tile has been read
-                for (int i = threadIdx.x; i < TW * TH; i += blockDim.x) {
-                    const int yy = div_small(i, TW), xx = i - yy * TW;
-                    const int gx = tx0 - r + xx, gy = ty0 - r + yy;
-                    const uint32_t sc = gx >= 0 && gx < J.w[k] && gy >= 0 && gy < J.h[k]
-                                            ? gload<uint16_t>(map + (ptrdiff_t)gy * mp + gx) : 0u;
-                    rank[i] = sc ? (sc << 16) | (0xFFFFu - (uint32_t)i) : 0u;
-                }
-                __syncthreads();
-                // row pass: the maximum over columns xx-r .. xx+r of every row
-                for (int i = threadIdx.x; i < tw * TH; i += blockDim.x) {
-                    const int yy = div_small(i, tw), xx = i - yy * tw;
-                    const uint32_t *q = rank + yy * TW + xx;   // columns xx .. xx+2r
-                    uint32_t m = q[0];
-                    for (int d = 1; d <= 2 * r; ++d) m = max(m, q[d]);
-                    hmax[i] = m;
-                }
-                __syncthreads();
-                // column pass over the tile's own pixels, then the cell keys
-                for (int i = threadIdx.x; i < tw * th; i += blockDim.x) {
-                    const int yy = div_small(i, tw), xx = i - yy * tw;
-                    const uint32_t own = rank[(yy + r) * TW + xx + r];
-                    if (own == 0) continue;
-                    uint32_t m = 0;
-                    for (int d = 0; d <= 2 * r; ++d) m = max(m, hmax[(yy + d) * tw + xx]);
-                    if (m != own) continue;
-                    const uint32_t sc = own >> 16;
-                    const int ox = tx0 + xx - x0, oy = ty0 + yy - y0;
-                    const int cx = div_small(ox, cw), cy = div_small(oy, cw);
-                    const uint32_t local = (uint32_t)((oy - cy * cw) * cw + (ox - cx * cw));
-                    const uint32_t key = (sc << 19) | ((uint32_t)(7 - k) << 16) | (0xFFFFu - local);
-                    atomicMax(&keys[cy * R.ncx + cx], key);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    keys_write(J, R, keys);
-}
-
 // The kernel arguments' cache lines, fetched together at a kernel's start.
 // They lie in host-visible memory and each costs a first access about 700
 // cycles; read where they are first used, they queue one behind the other
@@ -1506,6 +1433,238 @@ __device__ __forceinline__ void touch_arguments() {
     static_assert(sizeof(fg_job) + 16 <= 384, "the argument and the block size lie in six lines");
     const uint32_t a = p[0], b = p[16], c = p[32], d = p[48], e = p[64], f = p[80];
     asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+}
+
+// Standalone NMS over (2R+1) x (2R+1) neighbourhoods and the cell arg-max
+// across levels, from global score maps (J.smap).  One workgroup per region;
+// the region is walked in 64 x 64 sub-tiles, every level's part of a sub-tile
+// (64 >> k pixels a side) staged in LDS at once with an R-pixel halo (zero
+// outside the map).
+//
+// Few pixels score (about 2%), so the pixels that do are gathered into a list
+// as they are staged, and only they are compared with their windows: a pixel
+// survives when its score is above every earlier one of its window in
+// row-major order and not below any later one.  What bounds it is the chain
+// of one workgroup (load, gather, compare) and the maps' bytes.  Comparing
+// every pixel by separable window maxima, level after level, took 9.7 us for
+// 641x479 with 3 levels and R = 1, and 30.4 for 1920x1080 with 4 levels and
+// R = 4; this takes 6.7 and 10.2.  With every pixel of the second frame scoring
+// it takes 18.2 us at R = 1 and 23.6 at R = 4 (20.6 and 31.6 before).
+//
+// A map's rows start at any even address, so a row's 8-pixel chunks are loaded
+// from where they lie (16-byte loads at 2-byte alignment); a chunk across the
+// row's end is loaded from inside the row and shifted.
+constexpr int NMS_THREADS = 256;
+typedef u32x4 __attribute__((aligned(2))) u32x4_at2;
+
+// Elements gx .. gx+7 of a map row of W elements (zero outside it).
+__device__ __forceinline__ u32x4 map_chunk(const uint16_t *row, int W, int gx) {
+    if (gx >= W || gx + 8 <= 0) return u32x4{0u, 0u, 0u, 0u};
+    if (W < 8) {   // the row is shorter than a chunk
+        u32x4 v = {0u, 0u, 0u, 0u};
+        for (int x = max(gx, 0); x < W; ++x) {
+            const int e = x - gx;
+            if (e < 8) v[e >> 1] |= (uint32_t)gload<uint16_t>(row + x) << (16 * (e & 1));
+        }
+        return v;
+    }
+    const int at = min(max(gx, 0), W - 8), d = gx - at;
+    const u32x4 v = *(const GLOBAL u32x4_at2 *)(row + at);
+    if (d == 0) return v;
+    uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+    if (d < 0) {   // the first -d elements lie before the row
+        const int sh = 16 * -d;
+        hi = sh >= 64 ? lo << (sh - 64) : hi << sh | lo >> (64 - sh);
+        lo = sh >= 64 ? 0 : lo << sh;
+    } else {       // the last d lie past it
+        const int sh = 16 * d;
+        lo = sh >= 64 ? hi >> (sh - 64) : lo >> sh | hi << (64 - sh);
+        hi = sh >= 64 ? 0 : hi >> sh;
+    }
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// Level k's tile in LDS, at its largest: rows, row pitch and first element.
+template <int R>
+struct NmsTiles {
+    static constexpr int side(int k) { return (SUB >> k) > 0 ? SUB >> k : 1; }
+    static constexpr int rows(int k) { return side(k) + 2 * R; }
+    static constexpr int pitch(int k) { return (side(k) + 2 * R + 7) & ~7; }
+    static constexpr int first(int k) { return k == 0 ? 0 : first(k - 1) + rows(k - 1) * pitch(k - 1); }
+    // staging steps: threads take one chunk each
+    static constexpr int steps(int k) { return (rows(k) * (pitch(k) / 8) + NMS_THREADS - 1) / NMS_THREADS; }
+    static constexpr int pixels() {
+        int n = 0;
+        for (int k = 0; k < FAST_MAX_LEVELS; ++k) n += side(k) * side(k);
+        return n;
+    }
+    static constexpr int LIST = first(FAST_MAX_LEVELS) * 2;     // byte offset of the pixel list
+    static constexpr int KEYS = LIST + pixels() * 4;
+    static constexpr int BYTES = KEYS + MAX_KEYS * 4;
+    static_assert(LIST % 16 == 0, "16-byte tile stores");
+    static_assert(steps(0) == 3 && steps(1) == 1, "chunks a thread holds");
+};
+
+// A level's part of the sub-tile at (sx0, sy0), from (x0, y0) to (x1, y1).
+struct NmsPart {
+    int x0, y0, x1, y1;
+    __device__ NmsPart(const fg_job &J, const Region &R, int sx0, int sy0, int k) {
+        x0 = sx0 >> k;
+        y0 = sy0 >> k;
+        x1 = min(min((sx0 + SUB) >> k, R.xr1 >> k), J.w[k]);
+        y1 = min(min((sy0 + SUB) >> k, R.yr1 >> k), J.h[k]);
+    }
+    __device__ bool empty() const { return x1 <= x0 || y1 <= y0; }
+};
+
+// The score of a listed pixel if it wins its (2W+1) x (2W+1) window (W <= R),
+// else 0: it is above every earlier pixel in row-major order and not below any
+// later one.
+template <int R, int W>
+__device__ __forceinline__ uint32_t nms_peak(const uint16_t *tile, uint32_t entry) {
+    using L = NmsTiles<R>;
+    const int k = entry >> 16, yy = (entry >> 8) & 0xFF, xx = entry & 0xFF;
+    int first = 0, pitch = L::pitch(0);
+#pragma unroll
+    for (int l = 1; l < FAST_MAX_LEVELS; ++l) {
+        first = k == l ? L::first(l) : first;
+        pitch = k == l ? L::pitch(l) : pitch;
+    }
+    const uint16_t *q = tile + first + (yy - W) * pitch + xx - W;   // the window's corner
+    uint32_t s = 0, earlier = 0, later = 0;
+#pragma unroll
+    for (int dy = 0; dy <= 2 * W; ++dy) {
+        const auto row = lds_base(q + dy * pitch);
+#pragma unroll
+        for (int dx = 0; dx <= 2 * W; ++dx) {
+            const uint32_t x = row[dx];
+            if (dy == W && dx == W)
+                s = x;
+            else if (dy < W || (dy == W && dx < W))
+                earlier = max(earlier, x);
+            else
+                later = max(later, x);
+        }
+    }
+    return s > earlier && s >= later ? s : 0u;
+}
+
+template <int R>
+__global__ void __launch_bounds__(NMS_THREADS) nms_grid_kernel(fg_job J) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    __shared__ int s_count;
+    using L = NmsTiles<R>;
+    touch_arguments();
+    const Region rg = region_of(J, xcd_item(blockIdx.x, gridDim.x));
+    uint16_t *tile = (uint16_t *)smem;
+    uint32_t *list = (uint32_t *)(smem + L::LIST), *keys = (uint32_t *)(smem + L::KEYS);
+    keys_clear(keys, rg.ncx * rg.ncy);
+    const int lane = lane_id();
+    for (int sy0 = rg.P.ry0; sy0 < rg.yr1; sy0 += SUB) {
+        for (int sx0 = rg.P.rx0; sx0 < rg.xr1; sx0 += SUB) {
+            // this thread's chunks of every level: level 0 three, the others one
+            constexpr int N = FAST_MAX_LEVELS + 2;
+            u32x4 v[N];
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const int k = n < 3 ? 0 : n - 2;
+                v[n] = u32x4{0u, 0u, 0u, 0u};
+                if (k >= J.levels) continue;
+                const NmsPart p(J, rg, sx0, sy0, k);
+                const int nch = (p.x1 - p.x0 + 2 * R + 7) >> 3;
+                const int i = (int)threadIdx.x + (n < 3 ? n * NMS_THREADS : 0);
+                const int yy = div_small(i, max(nch, 1)), gy = p.y0 - R + yy;
+                if (p.empty() || gy >= p.y1 + R || gy < 0 || gy >= J.h[k]) continue;
+                v[n] = map_chunk(J.smap[k] + (ptrdiff_t)gy * J.smap_pitch[k], J.w[k],
+                                 p.x0 - R + 8 * (i - yy * nch));
+            }
+            __syncthreads();   // the previous sub-tile's tiles and list have been read
+            if (threadIdx.x == 0) s_count = 0;
+            // to LDS; bit j of a chunk's mask: its element 2j scores and is the
+            // part's own, bit 16 + j: element 2j + 1
+            uint32_t own[N];
+            int mine = 0;
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const int k = n < 3 ? 0 : n - 2;
+                own[n] = 0;
+                if (k >= J.levels) continue;
+                const NmsPart p(J, rg, sx0, sy0, k);
+                const int nch = (p.x1 - p.x0 + 2 * R + 7) >> 3;
+                const int i = (int)threadIdx.x + (n < 3 ? n * NMS_THREADS : 0);
+                const int yy = div_small(i, max(nch, 1)), xx = 8 * (i - yy * nch), gy = p.y0 - R + yy;
+                if (p.empty() || gy >= p.y1 + R) continue;
+                *(u32x4 *)(tile + L::first(k) + yy * L::pitch(k) + xx) = v[n];
+                if (gy < p.y0 || gy >= p.y1) continue;
+                auto ones = [](uint32_t x) {
+                    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x),
+                                                                                  u16x2{1, 1}));
+                };
+                const uint32_t m = ones(v[n].x) | ones(v[n].y) << 1 | ones(v[n].z) << 2 | ones(v[n].w) << 3;
+                // own elements: lo <= e < hi
+                const int lo = min(max(R - xx, 0), 8), hi = max(min(p.x1 - p.x0 + R - xx, 8), lo);
+                own[n] = m & (bit_range((lo + 1) >> 1, (hi + 1) >> 1) | bit_range(lo >> 1, hi >> 1) << 16);
+                mine += __builtin_popcount(own[n]);
+            }
+            __syncthreads();   // the count is zero
+            const int incl = wave_scan(mine);
+            int at = 0;
+            if (lane == 63) at = incl ? atomicAdd(&s_count, incl) : 0;
+            at = __builtin_amdgcn_readlane(at, 63) + incl - mine;
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const int k = n < 3 ? 0 : n - 2;
+                if (k >= J.levels) continue;
+                const NmsPart p(J, rg, sx0, sy0, k);
+                const int nch = (p.x1 - p.x0 + 2 * R + 7) >> 3;
+                const int i = (int)threadIdx.x + (n < 3 ? n * NMS_THREADS : 0);
+                uint32_t m = own[n];
+                if (!__any(m != 0)) continue;
+                const int yy = div_small(i, max(nch, 1)), xx = 8 * (i - yy * nch);
+                while (m) {   // entry: level, tile row, tile column
+                    const int j = __builtin_ctz(m);
+                    m &= m - 1;
+                    list[at++] = (uint32_t)(k << 16 | yy << 8 | (xx + (j < 16 ? 2 * j : 2 * (j - 16) + 1)));
+                }
+            }
+            __syncthreads();   // tiles and list are complete
+            // each wave takes a part of the list; with more than two rounds
+            // a thread (maps scored far denser than corners are), what
+            // loses inside its 3 x 3 neighbourhood leaves the list first
+            const int count = s_count, part = (count + NMS_THREADS / 64 - 1) / (NMS_THREADS / 64);
+            uint32_t *mylist = list + (threadIdx.x >> 6) * part;
+            int n = min(part, max(count - (int)(threadIdx.x >> 6) * part, 0));
+            if (R > 1 && count > 2 * NMS_THREADS) {
+                int kept = 0;
+                for (int i0 = 0; i0 < n; i0 += 64) {
+                    const uint32_t e = mylist[min(i0 + lane, n - 1)];
+                    const bool keep = i0 + lane < n && nms_peak<R, 1>(tile, e) != 0;
+                    const uint64_t bal = __ballot(keep);
+                    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                    wave_sync();
+                    if (keep) mylist[kept + rank] = e;
+                    wave_sync();
+                    kept += __popcll(bal);
+                }
+                n = kept;
+            }
+            for (int i = lane; i < n; i += 64) {
+                const uint32_t e = mylist[i];
+                const int k = e >> 16, yy = (e >> 8) & 0xFF, xx = e & 0xFF;
+                const uint32_t s = nms_peak<R, R>(tile, e);
+                if (s == 0) continue;
+                // position in the region at level k, then in its cell
+                const int ox = (sx0 >> k) + xx - R - (rg.P.rx0 >> k), oy = (sy0 >> k) + yy - R - (rg.P.ry0 >> k);
+                const int cw = J.cell >> k;
+                const int cx = div_small(ox, cw), cy = div_small(oy, cw);
+                const uint32_t local = (uint32_t)((oy - cy * cw) * cw + (ox - cx * cw));
+                atomicMax(&keys[cy * rg.ncx + cx], (s << 19) | ((uint32_t)(7 - k) << 16) | (0xFFFFu - local));
+            }
+        }
+    }
+    __syncthreads();
+    keys_write(J, rg, keys);
 }
 
 // One frame whose regions are single fused sub-tiles, workgroups of at least
@@ -1856,7 +2015,13 @@ hipError_t fg_launch_score_maps(const fg_job &j, const fg_launch &L, hipStream_t
 }
 
 hipError_t fg_launch_nms_grid(const fg_job &j, int radius, hipStream_t s) {
-    hipLaunchKernelGGL(nms_grid_kernel, dim3(j.rx * j.ry), dim3(256), nms_smem_bytes(), s, j, radius);
+    const dim3 grid(j.rx * j.ry), block(NMS_THREADS);
+    switch (radius) {
+        case 1: hipLaunchKernelGGL(nms_grid_kernel<1>, grid, block, NmsTiles<1>::BYTES, s, j); break;
+        case 2: hipLaunchKernelGGL(nms_grid_kernel<2>, grid, block, NmsTiles<2>::BYTES, s, j); break;
+        case 3: hipLaunchKernelGGL(nms_grid_kernel<3>, grid, block, NmsTiles<3>::BYTES, s, j); break;
+        default: hipLaunchKernelGGL(nms_grid_kernel<4>, grid, block, NmsTiles<4>::BYTES, s, j); break;
+    }
     return hipGetLastError();
 }
 
