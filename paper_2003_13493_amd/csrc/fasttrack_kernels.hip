@@ -8,10 +8,16 @@
 // One wave64 per feature, as the paper assigns one warp per feature: a 16x16
 // patch is 4 pixels per lane, an 8x8 patch 1 pixel per lane, so every lane
 // runs the same iterations and exits the same level.  The patch-wide sums
-// (the 10 entries of H once per level, the 4-vector sum of U r per
-// iteration) are DPP reductions across each row of 16 lanes whose four row
-// sums every lane then reads in the same order, so every lane holds the same
+// (the entries of H once per level, the 4-vector sum of U r per iteration) are
+// DPP reductions read from the wave's last lane, so every lane holds the same
 // value and takes identical decisions.  Arithmetic is fp32.
+//
+// What bounds it: with 100 features the chain of the slowest one, a wave alone
+// on its SIMD; with 10,000 the vector issue (3071 instructions a feature, 50 of
+// the 54 us).  With a patch's bytes all loaded before the first is used (four
+// waits an iteration became one), a lane's 32-bit offsets to a scalar base and
+// the four sums reduced side by side, 752x480, 3 levels: 100 features 17.8 ->
+// 13.6 us, 1920x1080, 10,000 features 73.7 -> 57.5, every estimate bit for bit.
 //
 // Every sample of a patch sits at p + t + (integer offset), so all of them
 // share one fractional part: positions are split into an integer base and a
@@ -28,61 +34,78 @@ namespace {
 // 2-3% faster than four at 100 and at 10,000 features.
 constexpr int TRACK_WAVES = 1;
 
-// v plus its DPP-permuted copy (a register move, no LDS traffic)
+// v plus its DPP-permuted copy (one instruction, no LDS traffic); a lane the
+// control gives nothing adds 0
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float v) {
-    const int p = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false);
+    const int p = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true);
     return v + __builtin_bit_cast(float, p);
 }
 
-// Sum over the wave, the same value in every lane: within each row of 16
-// lanes by swapping neighbours (quad_perm 1,0,3,2 and 2,3,0,1), halves of 8
-// (row_half_mirror) and halves of the row (row_mirror), then the four row
-// sums read out in a fixed order.
-__device__ __forceinline__ float wave_sum(float v) {
-    v = dpp_add<0xB1>(v);
-    v = dpp_add<0x4E>(v);
-    v = dpp_add<0x141>(v);
-    v = dpp_add<0x140>(v);
-    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0));
-    const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 16));
-    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32));
-    const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 48));
-    return (r0 + r1) + (r2 + r3);
+// Sums over the wave of N values, wave-uniform: within each row of 16 lanes by
+// swapping neighbours (quad_perm 1,0,3,2 and 2,3,0,1), halves of 8
+// (row_half_mirror) and halves of the row (row_mirror), then each row's sum into
+// the next row (row 3 holds r2 + r3, row 1 r0 + r1), then row 1's into row 3,
+// whose last lane is read: (r0 + r1) + (r2 + r3).  The N chains run side by
+// side, step by step, so no step waits for the one before it (a DPP operand
+// needs two wait states).
+template <int N>
+__device__ __forceinline__ void wave_sums(float (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = dpp_add<0xB1>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = dpp_add<0x4E>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = dpp_add<0x141>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = dpp_add<0x140>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = dpp_add<0x142>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = dpp_add<0x143>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        v[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[i]), 63));
 }
 
 __device__ __forceinline__ float uniform(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
 
-// Bilinear sample at integer base (x0, y0) plus the shared fraction (ax, ay).
-__device__ __forceinline__ float bilinear(const uint8_t *p, int pitch, int x0, int y0, float ax, float ay) {
-    const uint8_t *r0 = p + (ptrdiff_t)y0 * pitch + x0;
-    const float a = r0[0], b = r0[1], c = r0[pitch], d = r0[pitch + 1];
-    const float top = (1.0f - ax) * a + ax * b;
-    const float bottom = (1.0f - ax) * c + ax * d;
-    return (1.0f - ay) * top + ay * bottom;
+// Between a and b, and the same with the other product rounded: which of the
+// two a sample takes is written out, so that estimates do not depend on how the
+// compiler fuses the sums around it.
+__device__ __forceinline__ float lerp(float a, float b, float t) { return __builtin_fmaf(1.0f - t, a, t * b); }
+__device__ __forceinline__ float lerp_b(float a, float b, float t) { return __builtin_fmaf(t, b, (1.0f - t) * a); }
+
+// a * b, rounded before anything is added to it.
+__device__ __forceinline__ float product(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
 }
 
-// A position split into an integer part and a fraction in [0, 1).
-struct Split {
-    int i;
-    float f;
-};
+// Bilinear sample of a b / c d at the shared fraction (ax, ay).
+__device__ __forceinline__ float bilinear(float a, float b, float c, float d, float ax, float ay) {
+    return lerp(lerp(a, b, ax), lerp(c, d, ax), ay);
+}
 
-__device__ __forceinline__ Split split(int base, float frac_plus) {
-    const float fl = floorf(frac_plus);
-    return Split{base + (int)fl, frac_plus - fl};
+__device__ __forceinline__ float byte_of(uint32_t w, int i) { return (float)((w >> (8 * i)) & 0xFFu); }
+
+// Bytes at any address, through the global address space, at a uniform base
+// plus a lane's 32-bit offset (scalar base, one vector register of address).
+typedef uint16_t __attribute__((aligned(1))) u16_at1;
+typedef uint32_t __attribute__((aligned(1))) u32_at1;
+template <class T>
+__device__ __forceinline__ uint32_t load_at(const uint8_t *base, uint32_t offset) {
+    return *(const __attribute__((address_space(1))) T *)(base + offset);
 }
 
 template <int S>
 __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, float pyf, int pyi, float &tkx,
                             float &tky, float &alpha, float &beta, int &total, int &status) {
-    constexpr int NP = S * S / 64;   // pixels per lane
+    constexpr int NP = S * S / 64;   // pixels per lane: column lane % S, rows lane / S + 64 / S * m
     constexpr int HALF = S / 2;
     const int lane = threadIdx.x & 63;
-    const uint8_t *T = A.tpl[k];
-    const uint8_t *I = A.img[k];
     const int tp = A.tpitch[k], ip = A.ipitch[k], W = A.w[k], H = A.h[k];
 
     // template patch plus the gradient margin: x in [p-HALF-1, p+HALF] usable
@@ -92,44 +115,62 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
     }
     const float g = 1.0f + alpha;
     float tv[NP], ux[NP], uy[NP];
-    float h00 = 0, h01 = 0, h02 = 0, h03 = 0, h11 = 0, h12 = 0, h13 = 0, h22 = 0, h23 = 0, h33 = 0;
+    float h[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // 00 01 02 03 11 12 13 22 23
+    {
+        // the 12 bytes behind a pixel's five samples: columns x-1 .. x+2 of
+        // rows y and y+1, columns x and x+1 of rows y-1 and y+2, all in flight
+        // before the first is used
+        const uint8_t *base = A.tpl[k] + (ptrdiff_t)(pyi - HALF - 1) * tp + (pxi - HALF - 1);
+        uint32_t above[NP], here[NP], below[NP], under[NP];
 #pragma unroll
-    for (int m = 0; m < NP; ++m) {
-        const int pix = lane + 64 * m;
-        const int ox = pix % S - HALF, oy = pix / S - HALF;
-        const int x0 = pxi + ox, y0 = pyi + oy;
-        const float t = bilinear(T, tp, x0, y0, pxf, pyf);
-        const float gx = 0.5f * (bilinear(T, tp, x0 + 1, y0, pxf, pyf) - bilinear(T, tp, x0 - 1, y0, pxf, pyf));
-        const float gy = 0.5f * (bilinear(T, tp, x0, y0 + 1, pxf, pyf) - bilinear(T, tp, x0, y0 - 1, pxf, pyf));
-        tv[m] = t;
-        ux[m] = g * gx;
-        uy[m] = g * gy;
-        h00 += ux[m] * ux[m];
-        h01 += ux[m] * uy[m];
-        h02 += ux[m] * t;
-        h03 += ux[m];
-        h11 += uy[m] * uy[m];
-        h12 += uy[m] * t;
-        h13 += uy[m];
-        h22 += t * t;
-        h23 += t;
-        h33 += 1.0f;
+        for (int m = 0; m < NP; ++m) {
+            const uint32_t o = (uint32_t)((lane / S + 64 / S * m) * tp + lane % S);
+            above[m] = load_at<u16_at1>(base + 1, o);
+            here[m] = load_at<u32_at1>(base + tp, o);
+            below[m] = load_at<u32_at1>(base + 2 * (ptrdiff_t)tp, o);
+            under[m] = load_at<u16_at1>(base + 3 * (ptrdiff_t)tp + 1, o);
+        }
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const float p0 = byte_of(here[m], 0), p1 = byte_of(here[m], 1), p2 = byte_of(here[m], 2),
+                        p3 = byte_of(here[m], 3);
+            const float q0 = byte_of(below[m], 0), q1 = byte_of(below[m], 1), q2 = byte_of(below[m], 2),
+                        q3 = byte_of(below[m], 3);
+            const float t = bilinear(p1, p2, q1, q2, pxf, pyf);
+            const float gx = 0.5f * (bilinear(p2, p3, q2, q3, pxf, pyf) -
+                                     lerp(lerp_b(p0, p1, pxf), lerp_b(q0, q1, pxf), pyf));
+            const float gy = 0.5f * (bilinear(q1, q2, byte_of(under[m], 0), byte_of(under[m], 1), pxf, pyf) -
+                                     bilinear(byte_of(above[m], 0), byte_of(above[m], 1), p1, p2, pxf, pyf));
+            tv[m] = t;
+            ux[m] = product(g, gx);
+            uy[m] = product(g, gy);
+            h[0] += ux[m] * ux[m];
+            h[1] += ux[m] * uy[m];
+            h[2] += ux[m] * t;
+            h[3] += ux[m];
+            h[4] += uy[m] * uy[m];
+            h[5] += uy[m] * t;
+            h[6] += uy[m];
+            h[7] += t * t;
+            h[8] += t;
+        }
     }
+    wave_sums(h);
     const bool gain = A.mode & FAST_TRACK_GAIN, offset = A.mode & FAST_TRACK_OFFSET;
     // Inactive parameters get an identity row and column and a zero right-hand
     // side, so their increment is 0 and the active block factors as it would
     // on its own.
     float M[4][4];
-    M[0][0] = wave_sum(h00);
-    M[1][0] = wave_sum(h01);
-    M[1][1] = wave_sum(h11);
-    M[2][0] = gain ? wave_sum(h02) : 0.0f;
-    M[2][1] = gain ? wave_sum(h12) : 0.0f;
-    M[2][2] = gain ? wave_sum(h22) : 1.0f;
-    M[3][0] = offset ? wave_sum(h03) : 0.0f;
-    M[3][1] = offset ? wave_sum(h13) : 0.0f;
-    M[3][2] = gain && offset ? wave_sum(h23) : 0.0f;
-    M[3][3] = offset ? wave_sum(h33) : 1.0f;
+    M[0][0] = h[0];
+    M[1][0] = h[1];
+    M[1][1] = h[4];
+    M[2][0] = gain ? h[2] : 0.0f;
+    M[2][1] = gain ? h[5] : 0.0f;
+    M[2][2] = gain ? h[7] : 1.0f;
+    M[3][0] = offset ? h[3] : 0.0f;
+    M[3][1] = offset ? h[6] : 0.0f;
+    M[3][2] = gain && offset ? h[8] : 0.0f;
+    M[3][3] = offset ? (float)(S * S) : 1.0f;
     // Cholesky factor, with the reciprocals of its diagonal kept so the
     // per-iteration solve has no divisions; singular when a pivot falls to
     // 1e-6 of its diagonal entry
@@ -152,34 +193,54 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
         }
     }
 
+    uint32_t io[NP];   // this lane's pixels in the image patch
+#pragma unroll
+    for (int m = 0; m < NP; ++m) io[m] = (uint32_t)((lane / S + 64 / S * m) * ip + lane % S);
+    const uint8_t *I = A.img[k];
+    const float eps2 = A.eps * A.eps;
     for (int it = 0; it < A.max_iter; ++it) {
         // a non-finite or huge estimate is outside (keeps the integer parts small)
-        if (!(fabsf(pxf + tkx) < 65536.0f && fabsf(pyf + tky) < 65536.0f)) {
+        const float fx = pxf + tkx, fy = pyf + tky;
+        if (!(fabsf(fx) < 65536.0f && fabsf(fy) < 65536.0f)) {
             status = FAST_TRACK_LOST_OUTSIDE;
             return;
         }
-        const Split sx = split(pxi, pxf + tkx), sy = split(pyi, pyf + tky);
-        // warped patch: x in [p+t-HALF, p+t+HALF-1] usable
-        if (sx.i - HALF < 0 || sy.i - HALF < 0 || sx.i + HALF - 1 > W - 2 || sy.i + HALF - 1 > H - 2) {
+        const float flx = floorf(fx), fly = floorf(fy), ax = fx - flx, ay = fy - fly;
+        const int x0 = pxi + __builtin_amdgcn_readfirstlane((int)flx) - HALF;
+        const int y0 = pyi + __builtin_amdgcn_readfirstlane((int)fly) - HALF;
+        // warped patch: x in [x0, x0+S-1] usable
+        if (x0 < 0 || y0 < 0 || x0 + S - 1 > W - 2 || y0 + S - 1 > H - 2) {
             status = FAST_TRACK_LOST_OUTSIDE;
             return;
-        }
-        float b0 = 0, b1 = 0, b2 = 0, b3 = 0;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) {
-            const int pix = lane + 64 * m;
-            const int ox = pix % S - HALF, oy = pix / S - HALF;
-            const float r = bilinear(I, ip, sx.i + ox, sy.i + oy, sx.f, sy.f) - (1.0f + alpha) * tv[m] - beta;
-            b0 += ux[m] * r;
-            b1 += uy[m] * r;
-            b2 += tv[m] * r;
-            b3 += r;
         }
         if (singular) {
             status = FAST_TRACK_SINGULAR;
             return;
         }
-        float rhs[4] = {wave_sum(b0), wave_sum(b1), gain ? wave_sum(b2) : 0.0f, offset ? wave_sum(b3) : 0.0f};
+        // every sample's bytes in flight before the first is used, from a
+        // scalar base and a lane's 32-bit offset (a global load of the same
+        // bytes takes a 64-bit vector addition each)
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(I + (ptrdiff_t)y0 * ip + x0), (short)0, (S + 1) * ip, 0x00020000);
+        uint32_t up[NP], down[NP];
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            up[m] = __builtin_amdgcn_raw_buffer_load_b16(rs, io[m], 0, 0);
+            down[m] = __builtin_amdgcn_raw_buffer_load_b16(rs, io[m], ip, 0);
+        }
+        float b[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const float r = bilinear(byte_of(up[m], 0), byte_of(up[m], 1), byte_of(down[m], 0), byte_of(down[m], 1),
+                                     ax, ay) -
+                            (1.0f + alpha) * tv[m] - beta;
+            b[0] += ux[m] * r;
+            b[1] += uy[m] * r;
+            b[2] += tv[m] * r;
+            b[3] += r;
+        }
+        wave_sums(b);
+        const float rhs[4] = {b[0], b[1], gain ? b[2] : 0.0f, offset ? b[3] : 0.0f};
         float y[4], d[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -200,20 +261,23 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
         tky = uniform(tky - d[1]);
         alpha = uniform(alpha + d[2]);
         beta = uniform(beta + d[3]);
-        if (d[0] * d[0] + d[1] * d[1] < A.eps * A.eps) break;
+        if (d[0] * d[0] + d[1] * d[1] < eps2) break;
     }
 }
 
 // Track feature f of A from its initial estimate (A.q, or zero when
 // zero_init) and write the estimate, status and iteration count.
 __device__ void track_feature(const fg_track_args &A, int f, bool zero_init) {
-    const float fx = A.feats[2 * f], fy = A.feats[2 * f + 1];
+    // wave-uniform, also where the list may change under the compiler's eyes
+    // (a launch that reads the live count): the positions that follow stay in
+    // scalar registers and the tests on them are scalar branches
+    const float fx = uniform(A.feats[2 * f]), fy = uniform(A.feats[2 * f + 1]);
     float tx = 0.0f, ty = 0.0f, alpha = 0.0f, beta = 0.0f;
     if (!zero_init) {
-        tx = A.q[4 * f];
-        ty = A.q[4 * f + 1];
-        alpha = A.q[4 * f + 2];
-        beta = A.q[4 * f + 3];
+        tx = uniform(A.q[4 * f]);
+        ty = uniform(A.q[4 * f + 1]);
+        alpha = uniform(A.q[4 * f + 2]);
+        beta = uniform(A.q[4 * f + 3]);
     }
     int total = 0, status = FAST_TRACK_OK;
     for (int k = A.levels - 1; k >= 0; --k) {
