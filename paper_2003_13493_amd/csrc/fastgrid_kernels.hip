@@ -13,7 +13,7 @@
 // Detection of a sub-tile scores every pixel of its area plus a 1-pixel ring
 // at every level:
 //
-//   P1 compass test, 8 pixels per lane in packed 16-bit lanes.  An arc of N
+//   P1 compass test, 8 pixels per lane, four to a register.  An arc of N
 //      circle pixels contains floor(N/4) consecutive compass points (circle
 //      indices 0, 4, 8, 12) of its label.  The 8-pixel groups of all levels
 //      are dealt to the waves round-robin in rounds of 64.
@@ -191,30 +191,43 @@ __device__ __forceinline__ uint32_t runs8(uint32_t m, int n) {
     return m & (m >> (n - 1 - s1 - s2 - s4));
 }
 
-// Compass test of two pixels in packed 16-bit lanes; per lane >= 0 iff the
-// pixel may be a corner.  K = floor(N/4) consecutive points of (N, E, S, W)
-// must all be brighter than c+t (darker than c-t); the weakest value over the
-// best run is compared with the centre.
+// Threshold constants of the compass test, one byte per pixel (uniform).
+//
+// v_lerp_u8 halves the sum of two bytes, for four pixels at once, rounding down
+// or (third operand 1) up.  Of a circle point X and the centre C,
+// q = (X + (255 - C)) / 2 is 127.5 + (X - C) / 2 rounded, so X > C + t and
+// X < C - t are thresholds on q, and bit 7 of lerp(q, 256 - b) says q >= b:
+//   brighter       q >= 128 + ceil(t/2), exact when q is rounded up for odd t;
+//   not darker     q >= 128 - floor(t/2), which takes a point exactly t darker
+//                  for darker too (the filter only has to keep every corner).
+struct CompassT {
+    uint32_t round, bright, dark;
+};
+
+__device__ __forceinline__ CompassT compass_t(int t) {
+    return CompassT{(uint32_t)(t & 1) * 0x01010101u, (uint32_t)(128 - ((t + 1) >> 1)) * 0x01010101u,
+                    (uint32_t)(128 + (t >> 1)) * 0x01010101u};
+}
+
+// Compass test of the four pixels of C: bit 7 of a byte is set where the pixel
+// may be a corner (the other bits are not cleared).  K = floor(N/4) consecutive
+// points of (N, E, S, W) must all be brighter, or all darker.
 template <int K>
-__device__ __forceinline__ s16x2 compass(s16x2 C, s16x2 N, s16x2 E, s16x2 S, s16x2 W, s16x2 T1) {
-    s16x2 need_hi, need_lo;
-    if constexpr (K == 1) {
-        need_hi = vmax(vmax(N, S), vmax(E, W));
-        need_lo = vmin(vmin(N, S), vmin(E, W));
-    } else if constexpr (K == 2) {
-        // adjacent pairs (N,E) (E,S) (S,W) (W,N): (N or S) and (E or W)
-        need_hi = vmin(vmax(N, S), vmax(E, W));
-        need_lo = vmax(vmin(N, S), vmin(E, W));
-    } else if constexpr (K == 3) {
-        // any 3 of the 4 are consecutive: second smallest / second largest
-        const s16x2 lo1 = vmin(N, S), hi1 = vmax(N, S), lo2 = vmin(E, W), hi2 = vmax(E, W);
-        need_hi = vmin(vmax(lo1, lo2), vmin(hi1, hi2));
-        need_lo = vmax(vmin(hi1, hi2), vmax(lo1, lo2));
-    } else {
-        need_hi = vmin(vmin(N, S), vmin(E, W));
-        need_lo = vmax(vmax(N, S), vmax(E, W));
-    }
-    return vmax(need_hi - C, C - need_lo) - T1;
+__device__ __forceinline__ uint32_t compass4(uint32_t C, uint32_t N, uint32_t E, uint32_t S, uint32_t W,
+                                             const CompassT &T) {
+    auto q = [&](uint32_t x) { return __builtin_amdgcn_lerp(x, ~C, T.round); };
+    const uint32_t qn = q(N), qe = q(E), qs = q(S), qw = q(W);
+    auto bright = [&](uint32_t x) { return __builtin_amdgcn_lerp(x, T.bright, 0u); };
+    auto keep = [&](uint32_t x) { return __builtin_amdgcn_lerp(x, T.dark, 0u); };   // not darker
+    const uint32_t bn = bright(qn), be = bright(qe), bs = bright(qs), bw = bright(qw);
+    const uint32_t kn = keep(qn), ke = keep(qe), ks = keep(qs), kw = keep(qw);
+    if constexpr (K == 1) return bn | be | bs | bw | ~(kn & ke & ks & kw);
+    // adjacent pairs (N,E) (E,S) (S,W) (W,N): (N or S) and (E or W)
+    if constexpr (K == 2) return ((bn | bs) & (be | bw)) | ~((kn & ks) | (ke & kw));
+    // any 3 of the 4 are consecutive
+    if constexpr (K == 3)
+        return (bn & bs & (be | bw)) | (be & bw & (bn | bs)) | ~((kn | ks | (ke & kw)) & (ke | kw | (kn & ks)));
+    return (bn & be & bs & bw) | ~(kn | ke | ks | kw);
 }
 
 // Circle of radius 3 (Section II-D) in cyclic order, as LDS byte offsets.
@@ -477,28 +490,19 @@ __device__ __forceinline__ Px8 load8(const uint8_t *smem, uint32_t off) {
     return x;
 }
 
-// Compass test of the 8 pixels of x: bit j <- pixel 2j, bit 4+j <- pixel
-// 2j+1 (set = may be a corner).
+// Compass test of the 8 pixels of x: bit j <- pixel j (set = may be a corner).
+// 45 instructions; unpacked to 16-bit lanes, two pixels each, it took 71.
 template <int K>
-__device__ __forceinline__ uint32_t compass8(const Px8 &x, s16x2 T1) {
+__device__ __forceinline__ uint32_t compass8(const Px8 &x, const CompassT &T) {
     if constexpr (K > 0) {
-        const uint32_t r01 = as_u32(compass<K>(
-            pair(x.D1, x.D1, 0x0c010c00u), pair(x.N0, x.N0, 0x0c010c00u), pair(x.D2, x.D1, 0x0c040c03u),
-            pair(x.S0, x.S0, 0x0c010c00u), pair(x.D1, x.D0, 0x0c020c01u), T1));
-        const uint32_t r23 = as_u32(compass<K>(
-            pair(x.D1, x.D1, 0x0c030c02u), pair(x.N0, x.N0, 0x0c030c02u), pair(x.D2, x.D1, 0x0c060c05u),
-            pair(x.S0, x.S0, 0x0c030c02u), pair(x.D1, x.D0, 0x0c040c03u), T1));
-        const uint32_t r45 = as_u32(compass<K>(
-            pair(x.D2, x.D2, 0x0c010c00u), pair(x.N1, x.N1, 0x0c010c00u), pair(x.D3, x.D2, 0x0c040c03u),
-            pair(x.S1, x.S1, 0x0c010c00u), pair(x.D2, x.D1, 0x0c020c01u), T1));
-        const uint32_t r67 = as_u32(compass<K>(
-            pair(x.D2, x.D2, 0x0c030c02u), pair(x.N1, x.N1, 0x0c030c02u), pair(x.D3, x.D2, 0x0c060c05u),
-            pair(x.S1, x.S1, 0x0c030c02u), pair(x.D2, x.D1, 0x0c040c03u), T1));
-        // sign bit of each 16-bit lane = rejected; bit j <- pixel 2j,
-        // bit 4+j <- pixel 2j+1
-        const uint32_t sg = ((r01 >> 15) & 0x10001u) | ((r23 >> 14) & 0x20002u) |
-                            ((r45 >> 13) & 0x40004u) | ((r67 >> 12) & 0x80008u);
-        return ~(sg | (sg >> 12)) & 0xFFu;
+        auto east = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_alignbyte(hi, lo, 3); };
+        auto west = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_alignbyte(hi, lo, 1); };
+        const uint32_t a = compass4<K>(x.D1, x.N0, east(x.D2, x.D1), x.S0, west(x.D1, x.D0), T);
+        const uint32_t b = compass4<K>(x.D2, x.N1, east(x.D3, x.D2), x.S1, west(x.D2, x.D1), T);
+        // bits 0 and 4 of byte j: pixels j and 4 + j; the dot product adds
+        // byte j shifted by j
+        const uint32_t m = ((a >> 7) & 0x01010101u) | ((b >> 3) & 0x10101010u);
+        return __builtin_amdgcn_udot4(m, 0x08040201u, 0u, false);
     } else {
         return 0xFFu;
     }
@@ -507,11 +511,11 @@ __device__ __forceinline__ uint32_t compass8(const Px8 &x, s16x2 T1) {
 // LDS offset a lane with entry e reads (a safe one for NO_GROUP).
 __device__ __forceinline__ uint32_t entry_off(uint32_t e) { return e != NO_GROUP ? (e & 0x3FFFu) : SAFE_OFF; }
 
-// Bits b with lo <= b < hi (0 <= lo <= hi <= 4).
+// Bits b with lo <= b < hi (0 <= lo <= hi < 32).
 __device__ __forceinline__ uint32_t bit_range(int lo, int hi) { return (1u << hi) - (1u << lo); }
 
 // P1+P2: compass test of every scored pixel of every level, 8 pixels per
-// lane in packed 16-bit lanes.  The groups of all levels form one sequence
+// lane.  The groups of all levels form one sequence
 // dealt to the waves round-robin in rounds of 64, so every wave does the
 // same share whatever the level sizes; a wave tests two rounds at a time so
 // that the LDS reads of one overlap the arithmetic of the other.  Groups with
@@ -526,7 +530,7 @@ __device__ int collect(const uint8_t *smem, const Seg &s0, const Seg &s1, const 
                        bool cached, uint32_t e01, uint32_t e23, uint32_t *blist, uint16_t *list) {
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
     const GroupSeq q = group_seq(s0, s1, s2);
-    const s16x2 T1 = {(short)(t + 1), (short)(t + 1)};
+    const CompassT T1 = compass_t(t);
     const int stride = nwaves * 64;
     int nb = 0;
     // survivors go to nb + (survivors below the lane); the other lanes write
@@ -577,11 +581,10 @@ __device__ int collect(const uint8_t *smem, const Seg &s0, const Seg &s1, const 
         const int r = (int)(((uint32_t)rel * 18725u) >> 21);   // rel / LP
         const int c0 = rel - r * LP;
         const bool row_ok = r >= sel3(l, s0.r_lo, s1.r_lo, s2.r_lo) && r <= sel3(l, s0.r_hi, s1.r_hi, s2.r_hi);
-        // pixel p of the group (column c0 + p) is testable iff lo <= p < hi;
-        // bit b of the mask is pixel 2b (b < 4) or 2(b-4)+1
+        // pixel p of the group (column c0 + p) is testable iff lo <= p < hi
         const int lo = min(max(sel3(l, s0.c_lo, s1.c_lo, s2.c_lo) - c0, 0), 8);
         const int hi = max(min(max(sel3(l, s0.c_hi, s1.c_hi, s2.c_hi) - c0 + 1, 0), 8), lo);
-        const uint32_t valid = bit_range((lo + 1) >> 1, (hi + 1) >> 1) | (bit_range(lo >> 1, hi >> 1) << 4);
+        const uint32_t valid = bit_range(lo, hi);
         const uint32_t m = row_ok ? (w & valid) : 0u;
         const int cnt = __builtin_popcount(m);
         const int incl = wave_scan(cnt);
@@ -593,7 +596,7 @@ __device__ int collect(const uint8_t *smem, const Seg &s0, const Seg &s1, const 
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const int at = (m >> b) & 1u ? pos + __builtin_popcount(m & ((1u << b) - 1u)) : spare;
-            list[at] = (uint16_t)(base + (uint32_t)(((b & 3) << 1) | (b >> 2)));
+            list[at] = (uint16_t)(base + (uint32_t)b);
         }
     }
     return count;
