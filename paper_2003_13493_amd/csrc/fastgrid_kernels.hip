@@ -2011,7 +2011,26 @@ __global__ void __launch_bounds__(64) pyr_kernel(PyrArgs A) {
     pyr_store<1>(A, 4, 8 * blockIdx.x + lane, blockIdx.y, e);
 }
 
+// A submission's tables, from pinned host memory to their device copy, one
+// 8-byte word a thread.  Bound by one trip over the host link.  The copy engine
+// takes the stream from the kernels and back: a submission's upload cost 17 us
+// of the 85 of 8 mixed frames that way, 7 of 74 this way.  The loads are of system
+// scope, so they never see what an earlier submission left in a cache.
+__global__ void __launch_bounds__(256) upload_kernel(uint64_t *__restrict__ dst, const uint64_t *src, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n)
+        gstore<uint64_t>(dst + i, __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM));
+}
+
 }  // namespace
+
+hipError_t fg_launch_upload(void *dev, const void *host, size_t bytes, hipStream_t s) {
+    const int n = (int)(bytes / 8);
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(upload_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (uint64_t *)dev,
+                       (const uint64_t *)host, n);
+    return hipGetLastError();
+}
 
 void fg_job_layout(fg_job &j, const fg_launch &L) {
     j.gw = (j.w[0] + j.cell - 1) / j.cell;

@@ -41,6 +41,11 @@ struct TableSlot {
     uint64_t ticket = 0;           // last submission that used this slot
 };
 
+// Staging buffers are read by a kernel (fg_launch_upload) on whichever device
+// the context is on.
+constexpr unsigned STAGING = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+static_assert(sizeof(fg_item) % 8 == 0 && sizeof(fg_fe_job) % 8 == 0, "tables are whole 8-byte words");
+
 constexpr size_t items_offset(int njobs) { return (sizeof(fg_job) * (size_t)njobs + 15) & ~(size_t)15; }
 
 // The work items of a batch: one per region of every job, then one per upper
@@ -395,7 +400,7 @@ FG_API const char *fast_last_error(const fast_ctx *c) { return c ? c->err.c_str(
 // Staging buffers of a submission slot, `cap` bytes each, and its queue
 // counters (zeroed).
 int slot_alloc(fast_ctx *c, TableSlot &S, size_t cap) {
-    hipError_t e = hipHostMalloc((void **)&S.host, cap, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void **)&S.host, cap, STAGING);
     if (e != hipSuccess) { S.host = nullptr; return hip_fail(c, e, "hipHostMalloc job table"); }
     e = hipMalloc((void **)&S.dev, cap);
     if (e != hipSuccess) { S.dev = nullptr; return hip_fail(c, e, "hipMalloc job table"); }
@@ -449,7 +454,7 @@ FG_API int fast_ctx_create(int hip_device, fast_ctx **out) {
     // once per device, and the pinned buffer its tables are staged in
     uint8_t *dev_scratch = nullptr;
     hipError_t se = scratch_address(hip_device, &dev_scratch);
-    if (se == hipSuccess) se = hipHostMalloc((void **)&c->static_host, STATIC_BYTES, hipHostMallocDefault);
+    if (se == hipSuccess) se = hipHostMalloc((void **)&c->static_host, STATIC_BYTES, STAGING);
     if (se == hipSuccess) se = hipEventCreateWithFlags(&c->static_copied, hipEventDisableTiming);
     if (se != hipSuccess) {
         fast_ctx_destroy(c);
@@ -772,7 +777,7 @@ FG_API int fast_submit(fast_ctx *c, const fast_job *jobs, int njobs, void *strea
     const fg_item *items_dev = (const fg_item *)(S.dev + off);
     fill_items((const fg_job *)S.host, njobs, (fg_item *)(S.host + off));
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = hipMemcpyAsync(S.dev, S.host, bytes, hipMemcpyHostToDevice, s);
+    hipError_t e = fg_launch_upload(S.dev, S.host, bytes, s);
     if (e != hipSuccess) return hip_fail(c, e, "job table upload");
     e = fg_launch_batch(jobs_dev, items_dev, work.total, work.total_upper, work.max_levels,
                         work.all_single, S.counter, c->launch, s);
@@ -813,7 +818,7 @@ FG_API int fast_submit_static(fast_ctx *c, const fast_job *jobs, int njobs, void
     fill_items((const fg_job *)(host + STATIC_COUNTER_BYTES), njobs, (fg_item *)(host + off));
     hipStream_t s = (hipStream_t)stream;
     uint8_t *dev = c->static_dev;
-    hipError_t e = hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, s);
+    hipError_t e = fg_launch_upload(dev, host, bytes, s);
     if (e != hipSuccess) return hip_fail(c, e, "static table upload");
     e = hipEventRecord(c->static_copied, s);
     if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord (static staging)");
@@ -928,7 +933,7 @@ FG_API int fast_frontend_step(fast_ctx *c, const fast_frontend_job *jobs, int nj
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
     const size_t bytes = sizeof(fg_fe_job) * (size_t)njobs;
-    hipError_t e = hipMemcpyAsync(S.dev, S.host, bytes, hipMemcpyHostToDevice, s);
+    hipError_t e = fg_launch_upload(S.dev, S.host, bytes, s);
     if (e != hipSuccess) return hip_fail(c, e, "front-end table upload");
     e = fg_launch_frontend((const fg_fe_job *)S.dev, njobs, total_slots, s);
     if (e != hipSuccess) return hip_fail(c, e, "front-end launch");

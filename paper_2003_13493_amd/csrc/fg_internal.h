@@ -132,6 +132,10 @@ __host__ __device__ constexpr int fg_upper_regions(const fg_job &j) {
     return ((j.gw + c - 1) / c) * ((j.gh + c - 1) / c);
 }
 
+// Copy `bytes` (a multiple of 8) of coherent pinned host memory to device
+// memory by a kernel on `s`.
+hipError_t fg_launch_upload(void *dev, const void *host, size_t bytes, hipStream_t s);
+
 // Batched path: `jobs_dev` is a device copy of the jobs, whose region_base
 // fields are prefix sums.  items[0 .. total) lists every region of every job
 // once, in any order; items[total .. total + total_upper) lists every upper
