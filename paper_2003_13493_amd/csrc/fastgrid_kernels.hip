@@ -384,7 +384,10 @@ __device__ __forceinline__ void set_groups(Geo &g) {
 
 __device__ __forceinline__ bool has_area(const Geo &g) { return g.ex > g.sx && g.ey > g.sy; }
 
-__device__ __forceinline__ int sel3(int l, int a, int b, int c) { return l == 0 ? a : (l == 1 ? b : c); }
+template <class T>
+__device__ __forceinline__ T sel3(int l, T a, T b, T c) {
+    return l == 0 ? a : (l == 1 ? b : c);
+}
 
 // Scored area of one level in a sub-tile: rows [r0, r0 + nrows) of the tile
 // band, groups of 8 pixels from column gc0, ppr groups per row; pixels
@@ -445,13 +448,10 @@ __device__ __forceinline__ uint32_t group_entry(const Seg &s0, const Seg &s1, co
 }
 
 // Group entries of one lane for the (at most four) compass rounds it takes
-// when four or more waves share a sub-tile, two 16-bit entries per word.
-// Regions with the same staged geometry have the same entries, so the
-// pipelined kernel keeps them across regions; `key` names the geometry
-// (-1: not reusable).
+// when four or more waves share a sub-tile, two 16-bit entries per word.  All
+// whole regions have the same entries, so the pipelined kernel keeps those.
 struct GroupCache {
     uint32_t e01, e23;
-    int key;
 };
 
 // The words a compass test of 8 pixels reads: the 16 bytes around the group
@@ -707,57 +707,66 @@ __device__ void store_scores(const uint8_t *smem, const Geo &g, uint16_t *dst, i
     }
 }
 
-// Detect levels g0..g(nl-1) of the staged sub-tile (score maps zeroed) and
-// fold the survivors into the region's cell keys.  P1-P4 run on every wave
-// without workgroup barriers; one barrier makes all scores visible before
-// NMS.
-struct NoHook {
-    __device__ void operator()() const {}
+// A staged sub-tile for the passes: its levels' scored areas, and whether every
+// level's groups start 4 bytes past a multiple of 8 (uniform): true for fused
+// sub-tiles, whose origins are on the 16-pixel grid; the levels of an upper
+// region may start elsewhere.
+struct Segs {
+    Seg s0, s1, s2;
+    bool a8;
 };
 
-// `before` runs on every thread just before the barrier that separates
-// scoring from NMS, `after` just after it (the pipelined kernel uses them to
-// publish its next work item and to reuse the level-0 tile, which NMS no
-// longer reads).
-//
-// `cache` (workgroups of four or more waves only) keeps the compass group
-// entries across calls whose staged geometry has the same `cache_key`
-// (-1: recompute; FILLED: the caller has filled it).
-constexpr int FILLED = -2;
-template <class Before = NoHook, class After = NoHook>
-__device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Geo &g2, int nl,
-                           const Params &P, uint32_t *keys, GroupCache *cache = nullptr, int cache_key = FILLED,
-                           Before before = Before(), After after = After()) {
-    const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-    uint8_t *scratch = smem + OFF_WAVES + wave * wave_bytes(nwaves);
-    uint32_t *blist = (uint32_t *)scratch;
-    uint16_t *list = (uint16_t *)(scratch + blist_cap(nwaves) * 4);
-    const Seg s0 = make_seg(g0, has_area(g0));
-    const Seg s1 = make_seg(g1, nl > 1 && has_area(g1));
-    const Seg s2 = make_seg(g2, nl > 2 && has_area(g2));
-    if (cache && cache_key != FILLED &&
-        (cache_key < 0 || __builtin_amdgcn_readfirstlane(cache->key) != cache_key)) {
-        group_cache_fill(*cache, s0, s1, s2);
-        cache->key = cache_key;
-    }
-    const uint32_t ce01 = cache ? cache->e01 : 0u, ce23 = cache ? cache->e23 : 0u;
-    // every level's groups start 4 bytes past a multiple of 8 (uniform): true
-    // for fused sub-tiles, whose origins are on the 16-pixel grid; the levels
-    // of an upper region may start elsewhere
-    const bool a8 = ((s0.tbase + s0.gc0) & 7) == 4 && (!s1.n || ((s1.tbase + s1.gc0) & 7) == 4) &&
-                    (!s2.n || ((s2.tbase + s2.gc0) & 7) == 4);
+// The levels' score maps and cells.
+struct Maps {
+    LevelMap m0, m1, m2;
+};
+
+__device__ __forceinline__ Segs segs_of(const Geo &g0, const Geo &g1, const Geo &g2, int nl) {
+    Segs s;
+    s.s0 = make_seg(g0, has_area(g0));
+    s.s1 = make_seg(g1, nl > 1 && has_area(g1));
+    s.s2 = make_seg(g2, nl > 2 && has_area(g2));
+    s.a8 = ((s.s0.tbase + s.s0.gc0) & 7) == 4 && (!s.s1.n || ((s.s1.tbase + s.s1.gc0) & 7) == 4) &&
+           (!s.s2.n || ((s.s2.tbase + s.s2.gc0) & 7) == 4);
+    return s;
+}
+
+__device__ __forceinline__ Maps maps_of(const Geo &g0, const Geo &g1, const Geo &g2, const Params &P) {
+    Maps m;
+    m.m0 = level_map(g0, 0, T0, g0.sy, g0.ey, P);
+    m.m1 = level_map(g1, 96, T1 - 96 * LP, g1.sy, g1.ey, P);
+    m.m2 = level_map(g2, 96, T2 - 96 * LP, g2.sy, g2.ey, P);
+    return m;
+}
+
+// The wave's lists.
+__device__ __forceinline__ uint32_t *group_list(uint8_t *smem) {
+    return (uint32_t *)(smem + OFF_WAVES + (threadIdx.x >> 6) * wave_bytes(blockDim.x >> 6));
+}
+__device__ __forceinline__ uint16_t *pixel_list(uint8_t *smem) {
+    return (uint16_t *)((uint8_t *)group_list(smem) + blist_cap(blockDim.x >> 6) * 4);
+}
+
+// P1-P4 of a staged sub-tile whose score maps are zero, on every wave without
+// workgroup barriers: scores into the maps; the wave's scored pixels stay in
+// its list.  Returns their count.  With `cached` (workgroups of four or more
+// waves) the wave's group entries are e01 and e23 (GroupCache).
+__device__ __forceinline__ int score_phase(uint8_t *smem, const Segs &S, const Maps &M, const Params &P, bool cached,
+                                           uint32_t e01, uint32_t e23) {
+    uint32_t *blist = group_list(smem);
+    uint16_t *list = pixel_list(smem);
     int n1 = 0;
     auto run_collect = [&](auto aligned) {
         constexpr bool A = decltype(aligned)::value;
         switch (P.kc) {
-            case 0: n1 = collect<0, A>(smem, s0, s1, s2, P.t, cache != nullptr, ce01, ce23, blist, list); break;
-            case 1: n1 = collect<1, A>(smem, s0, s1, s2, P.t, cache != nullptr, ce01, ce23, blist, list); break;
-            case 2: n1 = collect<2, A>(smem, s0, s1, s2, P.t, cache != nullptr, ce01, ce23, blist, list); break;
-            case 3: n1 = collect<3, A>(smem, s0, s1, s2, P.t, cache != nullptr, ce01, ce23, blist, list); break;
-            default: n1 = collect<4, A>(smem, s0, s1, s2, P.t, cache != nullptr, ce01, ce23, blist, list); break;
+            case 0: n1 = collect<0, A>(smem, S.s0, S.s1, S.s2, P.t, cached, e01, e23, blist, list); break;
+            case 1: n1 = collect<1, A>(smem, S.s0, S.s1, S.s2, P.t, cached, e01, e23, blist, list); break;
+            case 2: n1 = collect<2, A>(smem, S.s0, S.s1, S.s2, P.t, cached, e01, e23, blist, list); break;
+            case 3: n1 = collect<3, A>(smem, S.s0, S.s1, S.s2, P.t, cached, e01, e23, blist, list); break;
+            default: n1 = collect<4, A>(smem, S.s0, S.s1, S.s2, P.t, cached, e01, e23, blist, list); break;
         }
     };
-    if (a8)
+    if (S.a8)
         run_collect(std::true_type());
     else
         run_collect(std::false_type());
@@ -771,9 +780,6 @@ __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Ge
     // 4096x2160 39.4 -> 39.0, the 64-frame batch 102.7 -> 101.6; with two rounds
     // it saves more than it takes: 39.6 and 102.6 us)
     const int n2 = n1 <= 64 ? n1 : pass_even8(smem, P.t, P.k8, list, n1);
-    const LevelMap m0 = level_map(g0, 0, T0, g0.sy, g0.ey, P);
-    const LevelMap m1 = level_map(g1, 96, T1 - 96 * LP, g1.sy, g1.ey, P);
-    const LevelMap m2 = level_map(g2, 96, T2 - 96 * LP, g2.sy, g2.ey, P);
     uint16_t *maps = (uint16_t *)smem;
     const int lane = lane_id();
     // P4: full segment test and score into the level's score map (one loop
@@ -786,8 +792,7 @@ __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Ge
                 const int l = e >> 14;
                 int row, col;
                 tile_rc(e & 0x3FFF, row, col);
-                maps[row * MP + col + sel3(l, m0.mbias, m1.mbias, m2.mbias)] =
-                    (uint16_t)s;
+                maps[row * MP + col + sel3(l, M.m0.mbias, M.m1.mbias, M.m2.mbias)] = (uint16_t)s;
             }
         }
     };
@@ -796,21 +801,19 @@ __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Ge
         case FAST_SCORE_MT: score_pass(std::integral_constant<int, FAST_SCORE_MT>()); break;
         default: score_pass(std::integral_constant<int, FAST_SCORE_SADB>()); break;
     }
-    before();
-    __syncthreads();   // every level's scores, ring included, are in the maps
-    after();
-    if (P.smap[0]) {   // score-map mode: the sub-tile's own scores, no NMS
-        store_scores(smem, g0, P.smap[0], P.spitch[0]);
-        if (nl > 1) store_scores(smem, g1, P.smap[1], P.spitch[1]);
-        if (nl > 2) store_scores(smem, g2, P.smap[2], P.spitch[2]);
-        __builtin_amdgcn_s_setprio(0);
-        return;
-    }
-    // P5: 3x3 NMS of the sub-tile's own pixels, then the cell keys.  A lane
-    // issues its nine score reads together, so the test costs one LDS round
-    // trip; a ring pixel (its own sub-tile suppresses it) reads around a
-    // fixed entry of the level-0 map instead and is masked off.
-    for (int i = lane; i < n2; i += 64) {
+    return n2;
+}
+
+// P5 after the workgroup's scores are complete: 3x3 NMS of the sub-tile's own
+// pixels among the wave's n2 listed ones, then the cell keys.  A lane issues
+// its nine score reads together, so the test costs one LDS round trip; a ring
+// pixel (its own sub-tile suppresses it) reads around a fixed entry of the
+// level-0 map instead and is masked off.  k0: the first level.
+__device__ __forceinline__ void nms_phase(uint8_t *smem, const Maps &M, int k0, int ncx, uint32_t *keys, int n2) {
+    const uint16_t *list = pixel_list(smem);
+    const uint16_t *maps = (const uint16_t *)smem;
+    const LevelMap &m0 = M.m0, &m1 = M.m1, &m2 = M.m2;
+    for (int i = lane_id(); i < n2; i += 64) {
         const uint16_t e = list[i];
         const int l = e >> 14;
         int row, col;
@@ -833,14 +836,120 @@ __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Ge
         const int oy = row + sel3(l, m0.yo, m1.yo, m2.yo);
         // exact: v + 0.5 is at least 0.5 / cw from a multiple of cw, far above
         // the error of the approximate reciprocal for v < 2^12
-        const float inv = l == 0 ? m0.inv_cw : (l == 1 ? m1.inv_cw : m2.inv_cw);
+        const float inv = sel3(l, m0.inv_cw, m1.inv_cw, m2.inv_cw);
         const int cy = (int)(((float)oy + 0.5f) * inv), cx = (int)(((float)ox + 0.5f) * inv);
         const uint32_t local = (uint32_t)((oy - cy * cw) * cw + (ox - cx * cw));
-        const uint32_t key = (s << 19) | ((uint32_t)(7 - (g0.k + l)) << 16) | (0xFFFFu - local);
-        atomicMax(&keys[cy * P.ncx + cx], key);
+        const uint32_t key = (s << 19) | ((uint32_t)(7 - (k0 + l)) << 16) | (0xFFFFu - local);
+        atomicMax(&keys[cy * ncx + cx], key);
     }
     __builtin_amdgcn_s_setprio(0);
 }
+
+// The sub-tile's own scores to the global maps (P.smap).
+__device__ __forceinline__ void store_maps(const uint8_t *smem, const Geo &g0, const Geo &g1, const Geo &g2, int nl,
+                                           const Params &P) {
+    store_scores(smem, g0, P.smap[0], P.spitch[0]);
+    if (nl > 1) store_scores(smem, g1, P.smap[1], P.spitch[1]);
+    if (nl > 2) store_scores(smem, g2, P.smap[2], P.spitch[2]);
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// Detect levels g0..g(nl-1) of the staged sub-tile (score maps zeroed) and fold
+// the survivors into the region's cell keys, or write its scores to the global
+// maps (P.smap).  One barrier makes all scores visible before NMS.  `cache`
+// (workgroups of four or more waves only): the group entries, filled by the
+// caller.
+__device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Geo &g2, int nl, const Params &P,
+                           uint32_t *keys, const GroupCache *cache = nullptr) {
+    const Segs S = segs_of(g0, g1, g2, nl);
+    const Maps M = maps_of(g0, g1, g2, P);
+    const int n2 = score_phase(smem, S, M, P, cache != nullptr, cache ? cache->e01 : 0u, cache ? cache->e23 : 0u);
+    __syncthreads();   // every level's scores, ring included, are in the maps
+    if (P.smap[0]) {   // score-map mode
+        store_maps(smem, g0, g1, g2, nl, P);
+        return;
+    }
+    nms_phase(smem, M, g0.k, P.ncx, keys, n2);
+}
+
+// The passes of a whole region of SIDE x SIDE pixels with NL levels, which most
+// regions of a frame are: everything but the testable columns and rows (the
+// region may lie at the frame's edge) and the cell side is a constant, which
+// takes the set-up of the general case, and the scalar registers that hold it,
+// off every region's path.  With it a region of the 64-frame batch takes 390
+// scalar instructions a wave instead of 660 (98.6 -> 90.0 us).
+// (rx0, ry0): the region's origin; W, H: level 0.
+template <int SIDE, int NL>
+struct Whole {
+    static constexpr int HALO = 4 << (NL - 1);   // the tile starts at the origin less (HALO + 15) & ~15 across
+    static constexpr int LEFT = (HALO + 15) & ~15;
+
+    // Level l < NL, in tile coordinates.
+    static constexpr Geo geo(int l) {
+        Geo g{};
+        g.tbase = l == 0 ? T0 : (l == 1 ? T1 : T2);
+        g.sx = LEFT >> l;
+        g.sy = HALO >> l;
+        g.ex = g.sx + (SIDE >> l);
+        g.ey = g.sy + (SIDE >> l);
+        g.moff = l == 0 ? OFF_M0 : (l == 1 ? OFF_M1 : OFF_M2);
+        g.mp = MP;
+        g.k = l;
+        g.gc0 = (g.sx - 1) & ~3;
+        g.ncolg = (g.ex + 1 - g.gc0 + 3) >> 2;
+        g.ncolg += g.ncolg & 1;
+        return g;
+    }
+    static_assert(((T0 + geo(0).gc0) & 7) == 4 && ((T1 + geo(1).gc0) & 7) == 4 && ((T2 + geo(2).gc0) & 7) == 4,
+                  "aligned compass row reads");
+
+    static __device__ __forceinline__ Seg seg(int l, int rx0, int ry0, int W, int H) {
+        const Geo g = geo(l);
+        Seg q;
+        q.tbase = g.tbase;
+        q.r0 = g.sy - 1;
+        q.nrows = l < NL ? g.ey - g.sy + 2 : 0;
+        q.gc0 = g.gc0;
+        q.ppr = g.ncolg >> 1;
+        q.n = q.nrows * q.ppr;
+        const int tx = (rx0 - LEFT) >> l, ty = (ry0 - HALO) >> l;
+        q.c_lo = max(g.sx - 1, 3 - tx);
+        q.c_hi = min(g.ex, (W >> l) - 4 - tx);
+        q.r_lo = max(q.r0, 3 - ty);
+        q.r_hi = min(q.r0 + q.nrows - 1, (H >> l) - 4 - ty);
+        return q;
+    }
+    static __device__ __forceinline__ Segs segs(int rx0, int ry0, int W, int H) {
+        return Segs{seg(0, rx0, ry0, W, H), seg(1, rx0, ry0, W, H), seg(2, rx0, ry0, W, H), true};
+    }
+    static __device__ __forceinline__ void fill(GroupCache &c) {
+        group_cache_fill(c, seg(0, 0, 0, 0, 0), seg(1, 0, 0, 0, 0), seg(2, 0, 0, 0, 0));
+    }
+
+    static __device__ __forceinline__ LevelMap map(int l, int cell) {
+        const Geo g = geo(l);
+        const int row0 = l == 0 ? 0 : 96, col0 = g.tbase - row0 * LP;   // the tile's corner in its band
+        LevelMap m;
+        m.mp = MP;
+        m.mbias = (g.moff >> 1) + (1 - g.sy - row0) * MP + 1 - g.sx - col0;
+        m.rlo = g.sy + row0;
+        m.rhi = g.ey + row0;
+        m.clo = g.sx + col0;
+        m.chi = g.ex + col0;
+        m.xo = -g.sx - col0;
+        m.yo = -g.sy - row0;
+        m.cw = cell >> l;
+        m.inv_cw = __builtin_amdgcn_rcpf((float)max(m.cw, 1));
+        return m;
+    }
+    static __device__ __forceinline__ Maps maps(int cell) { return Maps{map(0, cell), map(1, cell), map(2, cell)}; }
+
+    // Whether region R of J is one (R's origin is a multiple of 16).
+    template <class Region>
+    static __device__ __forceinline__ bool is(const fg_job &J, const Region &R) {
+        return R.xr1 - R.P.rx0 == SIDE && R.yr1 - R.P.ry0 == SIDE && min(J.levels, MAX_FUSED) == NL;
+    }
+};
 
 // Stage level pixels [tx, tx+tw) x [ty, ty+th) into an LDS tile with 16-byte
 // loads (tx % 16 == 0, so no chunk straddles the pitch; tw <= 128).  Chunks
@@ -1677,8 +1786,9 @@ __global__ void __launch_bounds__(NMS_THREADS) nms_grid_kernel(fg_job J) {
 // is the chain of one workgroup, not the throughput: barriers and LDS round
 // trips count, and a wave's instructions one by one (four cycles each).
 // `scores`: write score maps instead of selecting features.
-template <bool SCORES>
+template <bool SCORES, int SIDE, int NL>
 __device__ __forceinline__ void single_region(const fg_job &J, uint8_t *smem) {
+    using WR = Whole<SIDE, NL>;
     touch_arguments();
     Region R = region_of(J, xcd_item(blockIdx.x, gridDim.x));
     const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
@@ -1688,10 +1798,14 @@ __device__ __forceinline__ void single_region(const fg_job &J, uint8_t *smem) {
     zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
     if (!SCORES) keys_clear(keys, R.ncx * R.ncy);
     const int nl = fused_levels(J);
+    const bool full = WR::is(J, R);
     Geo g0, g1, g2;
     describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
     GroupCache cache;
-    group_cache_fill(cache, g0, g1, g2, nl);
+    if (full)
+        WR::fill(cache);
+    else
+        group_cache_fill(cache, g0, g1, g2, nl);
     if (SCORES) {
         for (int l = 0; l < MAX_FUSED; ++l) {
             R.P.smap[l] = J.smap[l < J.levels ? l : 0];
@@ -1701,20 +1815,32 @@ __device__ __forceinline__ void single_region(const fg_job &J, uint8_t *smem) {
     const int ch = threadIdx.x & 7, q = threadIdx.x >> 3;
     if (ch < (st.tw >> 4) && 4 * q < st.th) quad_commit(smem, T, q, ch, st, J, 0, nl, g1, g2);
     __syncthreads();
-    run_passes(smem, g0, g1, g2, nl, R.P, keys, &cache);
+    if (!full) {
+        run_passes(smem, g0, g1, g2, nl, R.P, keys, &cache);
+    } else {
+        const int n2 = score_phase(smem, WR::segs(R.P.rx0, R.P.ry0, J.w[0], J.h[0]), WR::maps(J.cell), R.P, true,
+                                   cache.e01, cache.e23);
+        __syncthreads();
+        if (SCORES)
+            store_maps(smem, g0, g1, g2, nl, R.P);
+        else
+            nms_phase(smem, WR::maps(J.cell), 0, R.ncx, keys, n2);
+    }
     if (SCORES) return;
     __syncthreads();
     keys_write(J, R, keys);
 }
 
+template <int SIDE, int NL>
 __global__ void __launch_bounds__(512) detect_single_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    single_region<false>(J, smem);
+    single_region<false, SIDE, NL>(J, smem);
 }
 
+template <int SIDE, int NL>
 __global__ void __launch_bounds__(512) score_single_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    single_region<true>(J, smem);
+    single_region<true, SIDE, NL>(J, smem);
 }
 
 __global__ void __launch_bounds__(512) score_plain_kernel(fg_job J) {
@@ -1819,7 +1945,10 @@ __device__ __forceinline__ void queue_exit(unsigned *counter) {
 //       earlier) to LDS, build its levels 1-2 from the registers into LDS
 //       and their planes, start loading the tile after it, then run NMS into
 //       the keys.
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
+// Three waves a SIMD, which the LDS of three workgroups a CU allows anyway: the
+// constants of a whole region then stay in registers (at four waves, 128
+// registers, 72 of them are spilled and the kernel takes 214 us instead of 90).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3, 3)))
 detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__ items, int total,
                     unsigned *counter) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -1843,17 +1972,17 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     fg_item prev{0u, 0u};
     bool have_prev = false;
     int b = 0;
-    GroupCache gcache{0u, 0u, -1};
+    using W3 = Whole<SUB, MAX_FUSED>;
+    GroupCache whole;
+    W3::fill(whole);
     while (item < total) {
         const fg_job &J = jobs[il.job];   // uniform: read through the scalar cache
         const Region R = region_of(J, (int)il.region);
-        const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
         uint32_t *keys = (uint32_t *)(smem + (b ? OFF_KEYS2 : OFF_KEYS));
+        const bool full = W3::is(J, R);
         __syncthreads();   // [A]
         zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
         keys_clear(keys, R.ncx * R.ncy);
-        Geo g0, g1, g2;
-        describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
         __syncthreads();   // [B]
         // thread 0 only, read only where it was set; left without a value
         // elsewhere so that no copy of the atomic's result (which would wait
@@ -1862,37 +1991,39 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
         // (the first lane of the last wave: wave 0 already carries the extra
         // compass round of a full region, so it sets the region's pace)
         if (threadIdx.x == blockDim.x - 64 && next < total) ticket = queue_ticket(q);
-        int after = total;
-        // the staged geometry depends only on the fused level count and the
-        // region's size once its origin is 16-aligned across and 4-aligned down
-        const int gkey = (R.P.rx0 & 15) == 0 && (R.P.ry0 & 3) == 0
-                             ? fused_levels(J) | (R.xr1 - R.P.rx0) << 2 | (R.yr1 - R.P.ry0) << 9
-                             : -1;
-        run_passes(
-            smem, g0, g1, g2, fused_levels(J), R.P, keys, &gcache, gkey,
-            [&]() {
-                if (threadIdx.x == blockDim.x - 64)
-                    s_next[b] = next < total ? queue_item(q, 2LL * q.n + ticket, total) : total;
-            },
-            [&]() {   // after [C]
-                after = __builtin_amdgcn_readfirstlane(s_next[b]);
-                if (next < total) {
-                    region_commit(smem, jobs[in.job], (int)in.region, T);
-                    if (after < total) {
-                        const fg_item ia = items[after];
-                        region_prefetch(jobs[ia.job], (int)ia.region, T);
-                    }
-                }
-                // the previous region's slots, written by the threads the
-                // tile commit leaves idle (quads past level-0 row 96); its
-                // keys buffer is next cleared after the next [A]
-                if (have_prev && threadIdx.x >= QUAD_THREADS) {
-                    const fg_job &Jp = jobs[prev.job];
-                    keys_write(Jp, region_of(Jp, (int)prev.region),
-                               (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)), threadIdx.x - QUAD_THREADS,
-                               blockDim.x - QUAD_THREADS);
-                }
-            });
+        int n2;
+        Geo g0, g1, g2;
+        if (full) {
+            n2 = score_phase(smem, W3::segs(R.P.rx0, R.P.ry0, J.w[0], J.h[0]), W3::maps(J.cell), R.P, true, whole.e01,
+                             whole.e23);
+        } else {
+            const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
+            describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
+            n2 = score_phase(smem, segs_of(g0, g1, g2, fused_levels(J)), maps_of(g0, g1, g2, R.P), R.P, false, 0u, 0u);
+        }
+        if (threadIdx.x == blockDim.x - 64)
+            s_next[b] = next < total ? queue_item(q, 2LL * q.n + ticket, total) : total;
+        __syncthreads();   // [C]
+        const int after = __builtin_amdgcn_readfirstlane(s_next[b]);
+        if (next < total) {
+            region_commit(smem, jobs[in.job], (int)in.region, T);
+            if (after < total) {
+                const fg_item ia = items[after];
+                region_prefetch(jobs[ia.job], (int)ia.region, T);
+            }
+        }
+        // the previous region's slots, written by the threads the tile commit
+        // leaves idle (quads past level-0 row 96); its keys buffer is next
+        // cleared after the next [A]
+        if (have_prev && threadIdx.x >= QUAD_THREADS) {
+            const fg_job &Jp = jobs[prev.job];
+            keys_write(Jp, region_of(Jp, (int)prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
+                       threadIdx.x - QUAD_THREADS, blockDim.x - QUAD_THREADS);
+        }
+        if (full)
+            nms_phase(smem, W3::maps(J.cell), 0, R.ncx, keys, n2);
+        else
+            nms_phase(smem, maps_of(g0, g1, g2, R.P), 0, R.ncx, keys, n2);
         prev = il;
         have_prev = true;
         item = next;
@@ -2086,17 +2217,28 @@ static hipError_t launch_upper(const fg_job &j, const fg_launch &L, bool scores,
 // can stage at once (24 quads of 8 threads).
 static bool single_regions(const fg_job &j, const fg_launch &L) { return j.rcells * j.cell <= SUB && L.block >= 256; }
 
-hipError_t fg_launch_plain(const fg_job &j, const fg_launch &L, hipStream_t s) {
-    hipLaunchKernelGGL(single_regions(j, L) ? detect_single_kernel : detect_plain_kernel, dim3(j.rx * j.ry), dim3(L.block),
-                       fg_smem_bytes(L.block), s, j);
-    const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_upper(j, L, false, s);
+// The kernel whose whole regions (Whole) are the frame's: 64 or 32 pixels a
+// side, which the default rule gives, three levels and more or one.  Regions of
+// another side or of two levels take the general set-up in it (1 to 3% slower).
+template <int SIDE>
+static void (*single_kernel(int levels, bool scores))(fg_job) {
+    if (levels == 1) return scores ? score_single_kernel<SIDE, 1> : detect_single_kernel<SIDE, 1>;
+    return scores ? score_single_kernel<SIDE, 3> : detect_single_kernel<SIDE, 3>;
 }
 
-hipError_t fg_launch_score_maps(const fg_job &j, const fg_launch &L, hipStream_t s) {
-    hipLaunchKernelGGL(single_regions(j, L) ? score_single_kernel : score_plain_kernel, dim3(j.rx * j.ry), dim3(L.block), fg_smem_bytes(L.block), s, j);
+static hipError_t launch_frame(const fg_job &j, const fg_launch &L, bool scores, hipStream_t s) {
+    const int side = j.rcells * j.cell;
+    void (*kernel)(fg_job) = scores ? score_plain_kernel : detect_plain_kernel;
+    if (single_regions(j, L)) kernel = side <= 32 ? single_kernel<32>(j.levels, scores) : single_kernel<SUB>(j.levels, scores);
+    hipLaunchKernelGGL(kernel, dim3(j.rx * j.ry), dim3(L.block), fg_smem_bytes(L.block), s, j);
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_upper(j, L, true, s);
+    return e != hipSuccess ? e : launch_upper(j, L, scores, s);
+}
+
+hipError_t fg_launch_plain(const fg_job &j, const fg_launch &L, hipStream_t s) { return launch_frame(j, L, false, s); }
+
+hipError_t fg_launch_score_maps(const fg_job &j, const fg_launch &L, hipStream_t s) {
+    return launch_frame(j, L, true, s);
 }
 
 hipError_t fg_launch_nms_grid(const fg_job &j, int radius, hipStream_t s) {
