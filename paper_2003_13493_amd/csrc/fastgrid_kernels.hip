@@ -1181,13 +1181,13 @@ struct Region {
     Params P;
 };
 
-__device__ __forceinline__ Region region_of(const fg_job &J, int region) {
+// The region in column rxi and row ryi of a job's regions; `whole`: it is known
+// not to be clipped.
+__device__ __forceinline__ Region region_at(const fg_job &J, int rxi, int ryi, bool whole = false) {
     Region R;
-    R.ryi = region < (1 << 21) ? div_small(region, J.rx) : region / J.rx;
-    R.rxi = region - R.ryi * J.rx;
+    R.rxi = rxi;
+    R.ryi = ryi;
     R.rcells = J.rcells;
-    R.ncx = min(J.rcells, J.gw - R.rxi * J.rcells);
-    R.ncy = min(J.rcells, J.gh - R.ryi * J.rcells);
     R.P.t = J.t;
     R.P.n = J.n;
     R.P.kind = J.score;
@@ -1196,12 +1196,35 @@ __device__ __forceinline__ Region region_of(const fg_job &J, int region) {
     R.P.kc = J.n >> 2;
     R.P.k8 = J.n >> 1;
     R.P.cell = J.cell;
-    R.P.rx0 = R.rxi * J.rcells * J.cell;
-    R.P.ry0 = R.ryi * J.rcells * J.cell;
+    if (whole) {   // FG_WHOLE
+        R.ncx = R.ncy = J.rcells;
+        R.P.rx0 = rxi * SUB;
+        R.P.ry0 = ryi * SUB;
+        R.xr1 = R.P.rx0 + SUB;
+        R.yr1 = R.P.ry0 + SUB;
+    } else {
+        R.ncx = min(J.rcells, J.gw - rxi * J.rcells);
+        R.ncy = min(J.rcells, J.gh - ryi * J.rcells);
+        R.P.rx0 = rxi * J.rcells * J.cell;
+        R.P.ry0 = ryi * J.rcells * J.cell;
+        R.xr1 = min(R.P.rx0 + R.ncx * J.cell, J.w[0]);
+        R.yr1 = min(R.P.ry0 + R.ncy * J.cell, J.h[0]);
+    }
     R.P.ncx = R.ncx;
-    R.xr1 = min(R.P.rx0 + R.ncx * J.cell, J.w[0]);
-    R.yr1 = min(R.P.ry0 + R.ncy * J.cell, J.h[0]);
     return R;
+}
+
+__device__ __forceinline__ Region item_region(const fg_job &J, uint32_t code) {
+    return region_at(J, (int)(code & (FG_WHOLE - 1)), (int)(code >> 16));
+}
+__device__ __forceinline__ Region whole_region(const fg_job &J, uint32_t code) {
+    return region_at(J, (int)(code & (FG_WHOLE - 1)), (int)(code >> 16), true);
+}
+
+// A job's regions in row-major order.
+__device__ __forceinline__ Region region_of(const fg_job &J, int region) {
+    const int ryi = region < (1 << 21) ? div_small(region, J.rx) : region / J.rx;
+    return region_at(J, region - ryi * J.rx, ryi);
 }
 
 __device__ __forceinline__ void keys_clear(uint32_t *keys, int n) {
@@ -1232,8 +1255,7 @@ __device__ void keys_write(const fg_job &J, const Region &R, const uint32_t *key
     }
 }
 
-__device__ void detect_region(const fg_job &J, int region, uint8_t *smem) {
-    const Region R = region_of(J, region);
+__device__ void detect_region(const fg_job &J, const Region &R, uint8_t *smem) {
     uint32_t *keys = (uint32_t *)(smem + OFF_KEYS);
     __syncthreads();   // previous region's slot writes have read the keys
     keys_clear(keys, R.ncx * R.ncy);
@@ -1402,12 +1424,13 @@ __device__ __forceinline__ void upper_commit(const UpperRows &u, uint8_t *tile, 
     store_piece(J.lvl[B], J.pitch[B], gy, gx + 8, (uint64_t)o.w << 32 | o.z, 8, g);
 }
 
-// An upper region: `region` in the row-major grid of fg_upper_cells cells.
-__device__ Region upper_region_of(const fg_job &J, int region) {
-    Region R = region_of(J, 0);   // the parameters every region shares
-    const int rc = fg_upper_cells(J.cell, J.rcells), urx = (J.gw + rc - 1) / rc;
-    R.ryi = region / urx;
-    R.rxi = region - R.ryi * urx;
+// The upper region in column rxi and row ryi of the grid of fg_upper_cells
+// cells.
+__device__ Region upper_region_at(const fg_job &J, int rxi, int ryi) {
+    Region R = region_at(J, 0, 0);   // the parameters every region shares
+    const int rc = fg_upper_cells(J.cell, J.rcells);
+    R.ryi = ryi;
+    R.rxi = rxi;
     R.rcells = rc;
     R.ncx = min(rc, J.gw - R.rxi * rc);
     R.ncy = min(rc, J.gh - R.ryi * rc);
@@ -1441,8 +1464,8 @@ __device__ __forceinline__ void upper_geo(const fg_job &J, const Region &R, int 
 // is a template argument because a by-value job indexed by a variable is copied
 // to scratch memory (13 us instead of 7.9 for a 1920x1080 frame).
 template <int B, bool SCORES>
-__device__ __forceinline__ void upper_region(const fg_job &J, int region, uint8_t *smem) {
-    Region R = upper_region_of(J, region);
+__device__ __forceinline__ void upper_region(const fg_job &J, int rxi, int ryi, uint8_t *smem) {
+    Region R = upper_region_at(J, rxi, ryi);
     constexpr int TOP = B + MAX_FUSED <= FAST_MAX_LEVELS ? MAX_FUSED : FAST_MAX_LEVELS - B;   // levels there can be
     const int F = min(J.levels - B, TOP);
     const int sx = R.P.rx0 >> B, sy = R.P.ry0 >> B;
@@ -1499,15 +1522,58 @@ __device__ __forceinline__ void upper_region(const fg_job &J, int region, uint8_
     keys_write(J, R, keys);
 }
 
-// Issue the level-0 tile loads of a single-fused-sub-tile region.
-__device__ __forceinline__ void region_prefetch(const fg_job &J, int region, TileRegs &T) {
-    const Region R = region_of(J, region);
-    quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1));
+// Stage of a whole region (FG_WHOLE).
+__device__ __forceinline__ Stage whole_stage(const Region &R) {
+    constexpr int HALO = 4 << (MAX_FUSED - 1);
+    return Stage{R.P.rx0 - HALO, R.P.ry0 - HALO, SUB + 2 * HALO, SUB + 2 * HALO};
 }
 
-// Commit a prefetched region's tile and build its levels 1-2 (quad_commit).
-__device__ __forceinline__ void region_commit(uint8_t *smem, const fg_job &J, int region, const TileRegs &T) {
-    const Region R = region_of(J, region);
+// Commit a whole region's quad (quad_commit).  Its level pieces lie whole
+// inside or outside the region, those of one quad together, so one test takes
+// the place of their clipping, and the planes are addressed from scalar bases.
+__device__ __forceinline__ void whole_commit(uint8_t *smem, const TileRegs &R, const fg_job &J, const Region &rg) {
+    const int ch = threadIdx.x & 7, q = threadIdx.x >> 3;
+    if (ch >= 6 || q >= 24) return;
+    uint8_t *t0 = smem + T0 + 4 * q * LP + 16 * ch;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *(u32x4 *)(t0 + j * LP) = R.v[j];
+    const u32x4 a = R.v[0], b = R.v[1], c = R.v[2], d = R.v[3];
+    const uint2 r0 = make_uint2(halve4(make_uint2(a.x, a.y), make_uint2(b.x, b.y)),
+                                halve4(make_uint2(a.z, a.w), make_uint2(b.z, b.w)));
+    const uint2 r1 = make_uint2(halve4(make_uint2(c.x, c.y), make_uint2(d.x, d.y)),
+                                halve4(make_uint2(c.z, c.w), make_uint2(d.z, d.w)));
+    const uint32_t l2 = halve4(r0, r1);
+    *(uint2 *)(smem + T1 + (2 * q) * LP + 8 * ch) = r0;
+    *(uint2 *)(smem + T1 + (2 * q + 1) * LP + 8 * ch) = r1;
+    *(uint32_t *)(smem + T2 + q * LP + 4 * ch) = l2;
+    // quads 4 .. 19 of chunk columns 1 .. 4 are the region's own
+    const uint32_t oy = (uint32_t)q - 4, ox = (uint32_t)ch - 1;
+    if (oy >= 16 || ox >= 4) return;
+    uint8_t *p1 = J.lvl[1] + (ptrdiff_t)(rg.P.ry0 >> 1) * J.pitch[1] + (rg.P.rx0 >> 1);
+    uint8_t *p2 = J.lvl[2] + (ptrdiff_t)(rg.P.ry0 >> 2) * J.pitch[2] + (rg.P.rx0 >> 2);
+    const uint32_t o1 = 2 * oy * (uint32_t)J.pitch[1] + 8 * ox;
+    gstore<uint64_t>(p1 + o1, (uint64_t)r0.y << 32 | r0.x);
+    gstore<uint64_t>(p1 + o1 + (uint32_t)J.pitch[1], (uint64_t)r1.y << 32 | r1.x);
+    gstore<uint32_t>(p2 + (oy * (uint32_t)J.pitch[2] + 4 * ox), l2);
+}
+
+// Issue the level-0 tile loads of an item's region (a single fused sub-tile).
+__device__ __forceinline__ void region_prefetch(const fg_job &J, uint32_t code, TileRegs &T) {
+    if (code & FG_WHOLE) {
+        quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], whole_stage(whole_region(J, code)));
+    } else {
+        const Region R = item_region(J, code);
+        quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1));
+    }
+}
+
+// Commit a prefetched region's tile and build its levels 1-2.
+__device__ __forceinline__ void region_commit(uint8_t *smem, const fg_job &J, uint32_t code, const TileRegs &T) {
+    if (code & FG_WHOLE) {
+        whole_commit(smem, T, J, whole_region(J, code));
+        return;
+    }
+    const Region R = item_region(J, code);
     const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
     Geo g0, g1, g2;
     describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
@@ -1850,7 +1916,7 @@ __global__ void __launch_bounds__(512) score_plain_kernel(fg_job J) {
 
 __global__ void __launch_bounds__(512) detect_plain_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    detect_region(J, xcd_item(blockIdx.x, gridDim.x), smem);
+    detect_region(J, region_of(J, xcd_item(blockIdx.x, gridDim.x)), smem);
 }
 
 // Levels B .. B+2 of one frame, one upper region per block.
@@ -1858,7 +1924,7 @@ template <int B, bool SCORES>
 __global__ void __launch_bounds__(512) upper_plain_kernel(fg_job J) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     touch_arguments();
-    upper_region<B, SCORES>(J, blockIdx.x, smem);
+    upper_region<B, SCORES>(J, blockIdx.x, blockIdx.y, smem);
 }
 
 // Levels B .. B+2 of the batch's jobs that have them, one listed upper region
@@ -1869,7 +1935,7 @@ __global__ void __launch_bounds__(512) upper_batch_kernel(const fg_job *__restri
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const fg_item it = items[blockIdx.x];
     const fg_job &J = jobs[it.job];
-    if (J.levels > B) upper_region<B, false>(J, (int)it.region, smem);
+    if (J.levels > B) upper_region<B, false>(J, (int)(it.region & 0xFFFFu), (int)(it.region >> 16), smem);
 }
 
 // Persistent batched detectors.  Work items are regions of all jobs (items[]
@@ -1966,9 +2032,9 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     fg_item il = items[item];
     fg_item in = next < total ? items[next] : fg_item{0u, 0u};
     TileRegs T;
-    region_prefetch(jobs[il.job], (int)il.region, T);
-    region_commit(smem, jobs[il.job], (int)il.region, T);
-    if (next < total) region_prefetch(jobs[in.job], (int)in.region, T);
+    region_prefetch(jobs[il.job], il.region, T);
+    region_commit(smem, jobs[il.job], il.region, T);
+    if (next < total) region_prefetch(jobs[in.job], in.region, T);
     fg_item prev{0u, 0u};
     bool have_prev = false;
     int b = 0;
@@ -1977,9 +2043,9 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     W3::fill(whole);
     while (item < total) {
         const fg_job &J = jobs[il.job];   // uniform: read through the scalar cache
-        const Region R = region_of(J, (int)il.region);
+        const bool full = il.region & FG_WHOLE;
+        const Region R = full ? whole_region(J, il.region) : item_region(J, il.region);
         uint32_t *keys = (uint32_t *)(smem + (b ? OFF_KEYS2 : OFF_KEYS));
-        const bool full = W3::is(J, R);
         __syncthreads();   // [A]
         zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
         keys_clear(keys, R.ncx * R.ncy);
@@ -2006,10 +2072,10 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
         __syncthreads();   // [C]
         const int after = __builtin_amdgcn_readfirstlane(s_next[b]);
         if (next < total) {
-            region_commit(smem, jobs[in.job], (int)in.region, T);
+            region_commit(smem, jobs[in.job], in.region, T);
             if (after < total) {
                 const fg_item ia = items[after];
-                region_prefetch(jobs[ia.job], (int)ia.region, T);
+                region_prefetch(jobs[ia.job], ia.region, T);
             }
         }
         // the previous region's slots, written by the threads the tile commit
@@ -2017,7 +2083,7 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
         // cleared after the next [A]
         if (have_prev && threadIdx.x >= QUAD_THREADS) {
             const fg_job &Jp = jobs[prev.job];
-            keys_write(Jp, region_of(Jp, (int)prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
+            keys_write(Jp, item_region(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
                        threadIdx.x - QUAD_THREADS, blockDim.x - QUAD_THREADS);
         }
         if (full)
@@ -2035,7 +2101,7 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     __syncthreads();
     if (have_prev) {   // the last region used the buffer before the final flip of b
         const fg_job &Jp = jobs[prev.job];
-        keys_write(Jp, region_of(Jp, (int)prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)));
+        keys_write(Jp, item_region(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)));
     }
     queue_exit(counter);
 }
@@ -2059,7 +2125,7 @@ __global__ void __launch_bounds__(512) detect_batch_generic_kernel(const fg_job 
         const int item = s_item;
         if (item >= total) break;
         const fg_item it = items[item];
-        detect_region(jobs[it.job], (int)it.region, smem);
+        detect_region(jobs[it.job], item_region(jobs[it.job], it.region), smem);
     }
     queue_exit(counter);
 }
@@ -2203,12 +2269,13 @@ hipError_t fg_launch_pyramid(const fg_job &j, hipStream_t s) {
 
 // The passes over levels MAX_FUSED.. of one frame, in order.
 static hipError_t launch_upper(const fg_job &j, const fg_launch &L, bool scores, hipStream_t s) {
-    const int n = fg_upper_regions(j);
+    const int c = fg_upper_cells(j.cell, j.rcells);
+    const dim3 n((j.gw + c - 1) / c, (j.gh + c - 1) / c);
     if (j.levels > 3)
-        hipLaunchKernelGGL((scores ? upper_plain_kernel<3, true> : upper_plain_kernel<3, false>), dim3(n),
+        hipLaunchKernelGGL((scores ? upper_plain_kernel<3, true> : upper_plain_kernel<3, false>), n,
                            dim3(L.block), fg_smem_bytes(L.block), s, j);
     if (j.levels > 6)
-        hipLaunchKernelGGL((scores ? upper_plain_kernel<6, true> : upper_plain_kernel<6, false>), dim3(n),
+        hipLaunchKernelGGL((scores ? upper_plain_kernel<6, true> : upper_plain_kernel<6, false>), n,
                            dim3(L.block), fg_smem_bytes(L.block), s, j);
     return hipGetLastError();
 }

@@ -367,17 +367,23 @@ void fill_items(const fg_job *table, int njobs, fg_item *items) {
         for (int j = 0; j < njobs; ++j) {
             const fg_job &J = table[j];
             const int side = J.rcells * J.cell;
-            for (int r = 0; r < J.rx * J.ry; ++r) {
-                const int x0 = (r % J.rx) * side, y0 = (r / J.rx) * side;
-                const bool whole = x0 + side <= J.w[0] && y0 + side <= J.h[0];
-                if (whole == (pass == 0)) items[n++] = fg_item{(uint32_t)j, (uint32_t)r};
+            const int wx = J.w[0] / side, wy = J.h[0] / side;   // whole regions across and down
+            const uint32_t flag = side == FG_SUB && J.levels >= FG_MAX_FUSED ? FG_WHOLE : 0u;
+            for (int y = 0; y < J.ry; ++y) {
+                const uint32_t row = (uint32_t)y << 16;
+                if (pass == 0 && y < wy)
+                    for (int x = 0; x < wx; ++x) items[n++] = fg_item{(uint32_t)j, row | flag | (uint32_t)x};
+                if (pass == 1)
+                    for (int x = y < wy ? wx : 0; x < J.rx; ++x) items[n++] = fg_item{(uint32_t)j, row | (uint32_t)x};
             }
         }
     }
     for (int j = 0; j < njobs; ++j) {
         const fg_job &J = table[j];
-        const int regions = J.levels > FG_MAX_FUSED ? fg_upper_regions(J) : 0;
-        for (int r = 0; r < regions; ++r) items[n++] = fg_item{(uint32_t)j, (uint32_t)r};
+        if (J.levels <= FG_MAX_FUSED) continue;
+        const int c = fg_upper_cells(J.cell, J.rcells);
+        for (int y = 0; y * c < J.gh; ++y)
+            for (int x = 0; x * c < J.gw; ++x) items[n++] = fg_item{(uint32_t)j, (uint32_t)y << 16 | (uint32_t)x};
     }
 }
 

@@ -104,11 +104,14 @@ constexpr int FG_COUNTER_WORDS = FG_EXIT_WORD + FG_QUEUE_STRIDE;
 // (and XCDs) finishing up to 2% apart.
 constexpr int FG_QUEUE_RUN = 16;
 
-// One work item of the batched kernel: a region of a job.
+// One work item of the batched kernels: a region of a job, its row << 16 | its
+// column (below 2^12 each), with FG_WHOLE set for a whole region of 64 x 64
+// pixels of a job of three levels and more.
 struct fg_item {
     uint32_t job;
     uint32_t region;
 };
+constexpr uint32_t FG_WHOLE = 1u << 15;
 
 // Pyramid levels detected from one level-0 load; each FG_MAX_FUSED levels
 // further up take one more pass (levels 3-5, then 6-7).
