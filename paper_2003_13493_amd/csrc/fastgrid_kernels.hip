@@ -341,6 +341,25 @@ __device__ __forceinline__ uint32_t full_score(const uint8_t *p, int t, int n) {
     if ((rb | rd) == 0) return 0;
     if constexpr (KIND == FAST_SCORE_MT) return (uint32_t)max_threshold(v, cv, n);
     if constexpr (KIND == FAST_SCORE_SADA) {
+        if (n >= 9) {
+            // only one side can have an arc: its circle is flipped where it is
+            // the darker one (255 - v above 255 - lo instead of v below lo),
+            // and the points on the arc are summed in 16-bit lanes, j and j+8
+            // side by side, each term times its bit of the arc
+            const uint32_t flip = rb ? 0u : 0x00FF00FFu;
+            const uint32_t th = rb ? hi : 255u - lo;
+            const u16x2 th2 = {(unsigned short)th, (unsigned short)th};
+            const uint32_t arc = arc_cover(rb | rd, n);   // point j at bit 15-j
+            const uint32_t on = (arc >> 8) | (arc & 0xFFu) << 16;   // j at bit 7-j, j+8 at bit 23-j
+            u16x2 sum = {0, 0};
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const u16x2 p = __builtin_bit_cast(u16x2, (v[j] | (v[j + 8] << 16)) ^ flip);
+                const u16x2 bit = __builtin_bit_cast(u16x2, (on >> (7 - j)) & 0x00010001u);
+                sum += __builtin_elementwise_sub_sat(p, th2) * bit;
+            }
+            return (uint32_t)sum.x + sum.y;
+        }
         const uint32_t cb = arc_cover(rb, n), cd = arc_cover(rd, n);
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
