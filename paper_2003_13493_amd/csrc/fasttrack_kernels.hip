@@ -198,6 +198,8 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
     for (int m = 0; m < NP; ++m) io[m] = (uint32_t)((lane / S + 64 / S * m) * ip + lane % S);
     const uint8_t *I = A.img[k];
     const float eps2 = A.eps * A.eps;
+    float pa[NP], pb[NP], pc[NP], pd[NP];   // the image patch at (px0, py0)
+    int px0 = -1, py0 = -1;
     for (int it = 0; it < A.max_iter; ++it) {
         // a non-finite or huge estimate is outside (keeps the integer parts small)
         const float fx = pxf + tkx, fy = pyf + tky;
@@ -217,23 +219,33 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
             status = FAST_TRACK_SINGULAR;
             return;
         }
-        // every sample's bytes in flight before the first is used, from a
+        // the patch's bytes, all in flight before the first is used, from a
         // scalar base and a lane's 32-bit offset (a global load of the same
-        // bytes takes a 64-bit vector addition each)
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(I + (ptrdiff_t)y0 * ip + x0), (short)0, (S + 1) * ip, 0x00020000);
-        uint32_t up[NP], down[NP];
+        // bytes takes a 64-bit vector addition each).  Steps soon are fractions
+        // of a pixel: the bytes of the last iteration mostly serve again
+        if (x0 != px0 || y0 != py0) {
+            px0 = x0;
+            py0 = y0;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(I + (ptrdiff_t)y0 * ip + x0), (short)0, (S + 1) * ip, 0x00020000);
+            uint32_t up[NP], down[NP];
 #pragma unroll
-        for (int m = 0; m < NP; ++m) {
-            up[m] = __builtin_amdgcn_raw_buffer_load_b16(rs, io[m], 0, 0);
-            down[m] = __builtin_amdgcn_raw_buffer_load_b16(rs, io[m], ip, 0);
+            for (int m = 0; m < NP; ++m) {
+                up[m] = __builtin_amdgcn_raw_buffer_load_b16(rs, io[m], 0, 0);
+                down[m] = __builtin_amdgcn_raw_buffer_load_b16(rs, io[m], ip, 0);
+            }
+#pragma unroll
+            for (int m = 0; m < NP; ++m) {
+                pa[m] = byte_of(up[m], 0);
+                pb[m] = byte_of(up[m], 1);
+                pc[m] = byte_of(down[m], 0);
+                pd[m] = byte_of(down[m], 1);
+            }
         }
         float b[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int m = 0; m < NP; ++m) {
-            const float r = bilinear(byte_of(up[m], 0), byte_of(up[m], 1), byte_of(down[m], 0), byte_of(down[m], 1),
-                                     ax, ay) -
-                            (1.0f + alpha) * tv[m] - beta;
+            const float r = bilinear(pa[m], pb[m], pc[m], pd[m], ax, ay) - (1.0f + alpha) * tv[m] - beta;
             b[0] += ux[m] * r;
             b[1] += uy[m] * r;
             b[2] += tv[m] * r;
