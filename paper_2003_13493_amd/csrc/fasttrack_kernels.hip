@@ -106,7 +106,11 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
     constexpr int NP = S * S / 64;   // pixels per lane: column lane % S, rows lane / S + 64 / S * m
     constexpr int HALF = S / 2;
     const int lane = threadIdx.x & 63;
+    const uint8_t *T = A.tpl[k], *I = A.img[k];
     const int tp = A.tpitch[k], ip = A.ipitch[k], W = A.w[k], H = A.h[k];
+    // the level's parameters in one wait: the compiler moves each load to its
+    // first use, where the wave waits for it again
+    asm volatile("" ::"s"(T), "s"(I), "s"(tp), "s"(ip), "s"(W), "s"(H));
 
     // template patch plus the gradient margin: x in [p-HALF-1, p+HALF] usable
     if (pxi - HALF - 1 < 0 || pyi - HALF - 1 < 0 || pxi + HALF > W - 2 || pyi + HALF > H - 2) {
@@ -120,7 +124,7 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
         // the 12 bytes behind a pixel's five samples: columns x-1 .. x+2 of
         // rows y and y+1, columns x and x+1 of rows y-1 and y+2, all in flight
         // before the first is used
-        const uint8_t *base = A.tpl[k] + (ptrdiff_t)(pyi - HALF - 1) * tp + (pxi - HALF - 1);
+        const uint8_t *base = T + (ptrdiff_t)(pyi - HALF - 1) * tp + (pxi - HALF - 1);
         uint32_t above[NP], here[NP], below[NP], under[NP];
 #pragma unroll
         for (int m = 0; m < NP; ++m) {
@@ -196,7 +200,6 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
     uint32_t io[NP];   // this lane's pixels in the image patch
 #pragma unroll
     for (int m = 0; m < NP; ++m) io[m] = (uint32_t)((lane / S + 64 / S * m) * ip + lane % S);
-    const uint8_t *I = A.img[k];
     const float eps2 = A.eps * A.eps;
     float pa[NP], pb[NP], pc[NP], pd[NP];   // the image patch at (px0, py0)
     int px0 = -1, py0 = -1;
