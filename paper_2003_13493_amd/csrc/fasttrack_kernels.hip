@@ -13,8 +13,8 @@
 // value and takes identical decisions.  Arithmetic is fp32.
 //
 // What bounds it: with 100 features the chain of the slowest one, a wave alone
-// on its SIMD; with 10,000 the vector issue (3071 instructions a feature, 50 of
-// the 54 us).  With a patch's bytes all loaded before the first is used (four
+// on its SIMD; with 10,000 the vector issue (2733 instructions a feature, 44
+// of the 47 us).  With a patch's bytes all loaded before the first is used (four
 // waits an iteration became one), a lane's 32-bit offsets to a scalar base and
 // the four sums reduced side by side, 752x480, 3 levels: 100 features 17.8 ->
 // 13.6 us, 1920x1080, 10,000 features 73.7 -> 57.5, every estimate bit for bit.
@@ -220,34 +220,36 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
 #pragma unroll
     for (int m = 0; m < NP; ++m) io[m] = (uint32_t)((lane / S + 64 / S * m) * ip + lane % S);
     const float eps2 = A.eps * A.eps;
-    float pa[NP], pb[NP], pc[NP], pd[NP];   // the image patch at (px0, py0)
-    int px0 = -1, py0 = -1;
+    float pa[NP], pb[NP], pc[NP], pd[NP];   // the image patch at the pixel (pxi + fpx, pyi + fpy)
+    float fpx = __builtin_nanf(""), fpy = fpx;
     for (int it = 0; it < A.max_iter; ++it) {
-        // a non-finite or huge estimate is outside (keeps the integer parts small)
         const float fx = pxf + tkx, fy = pyf + tky;
-        if (!(fabsf(fx) < 65536.0f && fabsf(fy) < 65536.0f)) {
-            status = FAST_TRACK_LOST_OUTSIDE;
-            return;
-        }
         const float flx = floorf(fx), fly = floorf(fy), ax = fx - flx, ay = fy - fly;
-        const int x0 = pxi + __builtin_amdgcn_readfirstlane((int)flx) - HALF;
-        const int y0 = pyi + __builtin_amdgcn_readfirstlane((int)fly) - HALF;
-        // warped patch: x in [x0, x0+S-1] usable
-        if (x0 < 0 || y0 < 0 || x0 + S - 1 > W - 2 || y0 + S - 1 > H - 2) {
-            status = FAST_TRACK_LOST_OUTSIDE;
-            return;
-        }
-        if (singular) {
-            status = FAST_TRACK_SINGULAR;
-            return;
-        }
         // the patch's bytes, all in flight before the first is used, from a
         // scalar base and a lane's 32-bit offset (a global load of the same
         // bytes takes a 64-bit vector addition each).  Steps soon are fractions
-        // of a pixel: the bytes of the last iteration mostly serve again
-        if (x0 != px0 || y0 != py0) {
-            px0 = x0;
-            py0 = y0;
+        // of a pixel: the bytes of the last iteration mostly serve again, and
+        // with them what was tested of their position (never for a NaN, which
+        // equals nothing)
+        if (!(flx == fpx && fly == fpy)) {
+            // a non-finite or huge estimate is outside (keeps the integer parts small)
+            if (!(fabsf(fx) < 65536.0f && fabsf(fy) < 65536.0f)) {
+                status = FAST_TRACK_LOST_OUTSIDE;
+                return;
+            }
+            const int x0 = pxi + __builtin_amdgcn_readfirstlane((int)flx) - HALF;
+            const int y0 = pyi + __builtin_amdgcn_readfirstlane((int)fly) - HALF;
+            // warped patch: x in [x0, x0+S-1] usable
+            if (x0 < 0 || y0 < 0 || x0 + S - 1 > W - 2 || y0 + S - 1 > H - 2) {
+                status = FAST_TRACK_LOST_OUTSIDE;
+                return;
+            }
+            if (singular) {
+                status = FAST_TRACK_SINGULAR;
+                return;
+            }
+            fpx = flx;
+            fpy = fly;
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)(I + (ptrdiff_t)y0 * ip + x0), (short)0, (S + 1) * ip, 0x00020000);
             uint32_t up[NP], down[NP];
@@ -291,10 +293,10 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
             d[i] = s * inv[i];
         }
         ++total;
-        tkx = uniform(tkx - d[0]);
-        tky = uniform(tky - d[1]);
-        alpha = uniform(alpha + d[2]);
-        beta = uniform(beta + d[3]);
+        tkx -= d[0];
+        tky -= d[1];
+        alpha += d[2];
+        beta += d[3];
         if (d[0] * d[0] + d[1] * d[1] < eps2) break;
     }
 }
