@@ -13,11 +13,13 @@
 // value and takes identical decisions.  Arithmetic is fp32.
 //
 // What bounds it: with 100 features the chain of the slowest one, a wave alone
-// on its SIMD; with 10,000 the vector issue (2733 instructions a feature, 44
-// of the 47 us).  With a patch's bytes all loaded before the first is used (four
-// waits an iteration became one), a lane's 32-bit offsets to a scalar base and
-// the four sums reduced side by side, 752x480, 3 levels: 100 features 17.8 ->
-// 13.6 us, 1920x1080, 10,000 features 73.7 -> 57.5, every estimate bit for bit.
+// on its SIMD; with 10,000 the vector issue (2642 instructions a feature, 43
+// of the 45 us).  With a patch's bytes all loaded before the first is used (four
+// waits an iteration became one), a lane's 32-bit offsets to a scalar base, the
+// sums reduced side by side, bytes and tests kept while the pixel position stays
+// and an iteration's four sums in one register, 752x480, 3 levels: 100 features
+// 18.7 -> 11.9 us, 1920x1080, 10,000 features 70.9 -> 44.6, every estimate bit for
+// bit.
 //
 // Every sample of a patch sits at p + t + (integer offset), so all of them
 // share one fractional part: positions are split into an integer base and a
@@ -42,6 +44,10 @@ __device__ __forceinline__ float dpp_add(float v) {
     return v + __builtin_bit_cast(float, p);
 }
 
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
 // Sums over the wave of N values, wave-uniform: within each row of 16 lanes by
 // swapping neighbours (quad_perm 1,0,3,2 and 2,3,0,1), halves of 8
 // (row_half_mirror) and halves of the row (row_mirror), then each row's sum into
@@ -64,8 +70,45 @@ __device__ __forceinline__ void wave_sums(float (&v)[N]) {
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = dpp_add<0x143>(v[i]);
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-        v[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[i]), 63));
+    for (int i = 0; i < N; ++i) v[i] = lane_value(v[i], 63);
+}
+
+// v plus itself with even and odd rows of 16 lanes, or the wave's halves, swapped.
+__device__ __forceinline__ float add_rows(float v) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ float add_halves(float v) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+// Sums over quads of four values, value (lane & 3) in each lane: neighbours are
+// added (quad_perm 1,0,3,2), even lanes keep one value of a pair and odd ones
+// the other, and the same two lanes apart (2,3,0,1).
+__device__ __forceinline__ float quad_sums(float a, float b, float c, float d) {
+    const int lane = threadIdx.x & 63;
+    a = dpp_add<0xB1>(a);
+    b = dpp_add<0xB1>(b);
+    c = dpp_add<0xB1>(c);
+    d = dpp_add<0xB1>(d);
+    const float ab = lane & 1 ? b : a, cd = lane & 1 ? d : c;
+    const float abab = dpp_add<0x4E>(ab), cdcd = dpp_add<0x4E>(cd);
+    return lane & 2 ? cdcd : abab;
+}
+
+// wave_sums of an iteration's four values, the same additions in 17 instructions
+// instead of 24: once quads are summed one register holds all four.  Quads are
+// added to the quad before (row_ror:4) and two before (row_ror:8), which in odd
+// quads is (q0 + q1) + (q2 + q3), then rows and halves, (r0 + r1) + (r2 + r3).
+// 10,000 features 46.7 -> 44.4 us, 100 alike.
+__device__ __forceinline__ void wave_sums4(float (&b)[4]) {
+    float v = dpp_add<0x124>(quad_sums(b[0], b[1], b[2], b[3]));
+    v = add_halves(add_rows(dpp_add<0x128>(v)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = lane_value(v, 4 + i);
 }
 
 __device__ __forceinline__ float uniform(float v) {
@@ -275,7 +318,7 @@ __device__ void track_level(const fg_track_args &A, int k, float pxf, int pxi, f
             b[2] += tv[m] * r;
             b[3] += r;
         }
-        wave_sums(b);
+        wave_sums4(b);
         const float rhs[4] = {b[0], b[1], gain ? b[2] : 0.0f, offset ? b[3] : 0.0f};
         float y[4], d[4];
 #pragma unroll
