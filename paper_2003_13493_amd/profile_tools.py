@@ -92,9 +92,12 @@ def kernel_source_hash(names=DETECT_SOURCES) -> str:
 
 
 def short_name(name: str) -> str:
-    for key in ("detect_batch_kernel", "detect_plain_kernel", "pyr_batch_kernel", "pyr_kernel"):
+    for key in ("detect_batch_kernel", "detect_single_kernel", "detect_plain_kernel", "upper_batch_kernel",
+                "upper_plain_kernel", "pyr_kernel"):
         if key + "(" in name:
             return key
+        if key + "<" in name:   # with its template arguments
+            return name[name.index(key):name.index("(", name.index(key))]
     if "FillFunctor" in name:
         return "torch fill (harness)"
     return name[:60]
@@ -110,7 +113,7 @@ def trace_md(stats_csv: str, command: str) -> str:
         "Command (repo root):", "", "    " + command, "",
         f"Summary: `python -m paper_2003_13493_amd.profile_tools trace {stats_csv}`.",
         "detect_batch_kernel is one persistent launch over the whole 64-frame batch (pyramid levels 1-2",
-        "are built inside it); detect_plain_kernel is the plain path, one launch per frame.",
+        "are built inside it); detect_single_kernel is the plain path, one launch per frame.",
         f"Kernel source hash (sha256[:16] of the kernel and runtime sources without comments, and the hipcc flags) = {kernel_source_hash()}.", "", *lines, ""])
 
 
