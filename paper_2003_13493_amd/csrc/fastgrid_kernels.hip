@@ -467,8 +467,9 @@ __device__ __forceinline__ uint32_t group_entry(const Seg &s0, const Seg &s1, co
 }
 
 // Group entries of one lane for the (at most four) compass rounds it takes
-// when four or more waves share a sub-tile, two 16-bit entries per word.  All
-// whole regions have the same entries, so the pipelined kernel keeps those.
+// when four or more waves share a sub-tile, two 16-bit entries per word.
+// Regions of the same staged geometry have the same entries (all whole ones
+// do), so the pipelined kernels keep them.
 struct GroupCache {
     uint32_t e01, e23;
 };
@@ -1250,8 +1251,16 @@ __device__ __forceinline__ Region region_at(const fg_job &J, int rxi, int ryi, b
     return R;
 }
 
+// The region of an item, its column (and with VROW its row) in a vector register,
+// and with it what follows from it: of the general set-up's hundred words that
+// are the same in every lane, more are spilled and reloaded lane by lane in the
+// passes when all compete for the scalar registers.
+template <bool VROW>
 __device__ __forceinline__ Region item_region(const fg_job &J, uint32_t code) {
-    return region_at(J, (int)(code & (FG_WHOLE - 1)), (int)(code >> 16));
+    int column = (int)(code & (FG_WHOLE - 1)), row = (int)(code >> 16);
+    asm("" : "+v"(column));
+    if (VROW) asm("" : "+v"(row));
+    return region_at(J, column, row);
 }
 __device__ __forceinline__ Region whole_region(const fg_job &J, uint32_t code) {
     return region_at(J, (int)(code & (FG_WHOLE - 1)), (int)(code >> 16), true);
@@ -1594,22 +1603,24 @@ __device__ __forceinline__ void whole_commit(uint8_t *smem, const TileRegs &R, c
 }
 
 // Issue the level-0 tile loads of an item's region (a single fused sub-tile).
+template <bool WHOLE>
 __device__ __forceinline__ void region_prefetch(const fg_job &J, uint32_t code, TileRegs &T) {
-    if (code & FG_WHOLE) {
+    if (WHOLE && (code & FG_WHOLE)) {
         quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], whole_stage(whole_region(J, code)));
     } else {
-        const Region R = item_region(J, code);
+        const Region R = item_region<WHOLE>(J, code);
         quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1));
     }
 }
 
 // Commit a prefetched region's tile and build its levels 1-2.
+template <bool WHOLE>
 __device__ __forceinline__ void region_commit(uint8_t *smem, const fg_job &J, uint32_t code, const TileRegs &T) {
-    if (code & FG_WHOLE) {
+    if (WHOLE && (code & FG_WHOLE)) {
         whole_commit(smem, T, J, whole_region(J, code));
         return;
     }
-    const Region R = item_region(J, code);
+    const Region R = item_region<WHOLE>(J, code);
     const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
     Geo g0, g1, g2;
     describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
@@ -2033,7 +2044,7 @@ __device__ __forceinline__ void queue_exit(unsigned *counter) {
     }
 }
 
-// Pipelined kernel, for batches whose regions are all single fused sub-tiles
+// Pipelined kernels, for batches whose regions are all single fused sub-tiles
 // and workgroups of at least 256 threads (32 quads of tile rows cover a
 // fused tile).  Per region there are three workgroup barriers:
 //   [A] the previous region's NMS is done; this region's levels 0-2 are in
@@ -2047,17 +2058,14 @@ __device__ __forceinline__ void queue_exit(unsigned *counter) {
 //       and their planes, start loading the tile after it, write the previous
 //       region's slots by the threads the commit leaves idle, then run NMS into
 //       the keys.
-// What bounds it: vector issue two thirds of the time (1295 vector instructions a
-// wave and region) and, between the three barriers, the latency of LDS and of the
-// chains.  With whole regions' geometry constant, the compass by byte averages and
-// the sums in 16-bit lanes the 64-frame batch went from 103 to 89 us.
-// Three waves a SIMD, which the LDS of three workgroups a CU allows anyway: the
-// constants of a whole region then stay in registers (at four waves, 128
-// registers, 72 of them are spilled and the kernel takes 214 us instead of 90).
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3, 3)))
-detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__ items, int total,
-                    unsigned *counter) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+// With WHOLE, whole regions have a path on constant geometry; the others' general
+// one then sets up past [B] and keeps no group entries, which would take the
+// registers that the whole ones' constants live in (64 frames of three levels 93.8 us,
+// 96.1 with them).  Without it, group entries are kept while the staged geometry stays,
+// and the set-up hides under the clearing.
+template <bool WHOLE>
+__device__ __forceinline__ void batch_regions(const fg_job *__restrict__ jobs, const fg_item *__restrict__ items,
+                                              int total, unsigned *counter, uint8_t *smem) {
     // s_next[b] carries the item after next from its ticket's lane to the workgroup;
     // the two buffers alternate, so a value is never overwritten before every
     // wave has read it.
@@ -2072,23 +2080,30 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     fg_item il = items[item];
     fg_item in = next < total ? items[next] : fg_item{0u, 0u};
     TileRegs T;
-    region_prefetch(jobs[il.job], il.region, T);
-    region_commit(smem, jobs[il.job], il.region, T);
-    if (next < total) region_prefetch(jobs[in.job], in.region, T);
+    region_prefetch<WHOLE>(jobs[il.job], il.region, T);
+    region_commit<WHOLE>(smem, jobs[il.job], il.region, T);
+    if (next < total) region_prefetch<WHOLE>(jobs[in.job], in.region, T);
     fg_item prev{0u, 0u};
     bool have_prev = false;
     int b = 0;
     using W3 = Whole<SUB, MAX_FUSED>;
-    GroupCache whole;
-    W3::fill(whole);
+    GroupCache cache{0u, 0u};   // with WHOLE, the whole regions' entries; without, those of geometry cache_key
+    if (WHOLE) W3::fill(cache);
+    int cache_key = -1;
     while (item < total) {
         const fg_job &J = jobs[il.job];   // uniform: read through the scalar cache
-        const bool full = il.region & FG_WHOLE;
-        const Region R = full ? whole_region(J, il.region) : item_region(J, il.region);
+        const bool full = WHOLE && (il.region & FG_WHOLE);
+        const Region R = full ? whole_region(J, il.region) : item_region<WHOLE>(J, il.region);
         uint32_t *keys = (uint32_t *)(smem + (b ? OFF_KEYS2 : OFF_KEYS));
         __syncthreads();   // [A]
         zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
         keys_clear(keys, R.ncx * R.ncy);
+        Geo g0, g1, g2;
+        auto set_up = [&]() {
+            const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
+            describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
+        };
+        if (!WHOLE) set_up();
         __syncthreads();   // [B]
         // one lane only, read only where it was set; left without a value
         // elsewhere so that no copy of the atomic's result (which would wait
@@ -2098,24 +2113,32 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
         // compass round of a full region, so it sets the region's pace)
         if (threadIdx.x == blockDim.x - 64 && next < total) ticket = queue_ticket(q);
         int n2;
-        Geo g0, g1, g2;
         if (full) {
-            n2 = score_phase(smem, W3::segs(R.P.rx0, R.P.ry0, J.w[0], J.h[0]), W3::maps(J.cell), R.P, true, whole.e01,
-                             whole.e23);
+            n2 = score_phase(smem, W3::segs(R.P.rx0, R.P.ry0, J.w[0], J.h[0]), W3::maps(J.cell), R.P, true, cache.e01,
+                             cache.e23);
         } else {
-            const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
-            describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
-            n2 = score_phase(smem, segs_of(g0, g1, g2, fused_levels(J)), maps_of(g0, g1, g2, R.P), R.P, false, 0u, 0u);
+            if (WHOLE) set_up();
+            const Segs S = segs_of(g0, g1, g2, fused_levels(J));
+            if (!WHOLE) {
+                // the staged geometry depends only on the fused level count and the
+                // region's size: its origin is 16-aligned
+                const int key = fused_levels(J) | (R.xr1 - R.P.rx0) << 2 | (R.yr1 - R.P.ry0) << 9;
+                if (__builtin_amdgcn_readfirstlane(cache_key ^ key)) {
+                    group_cache_fill(cache, S.s0, S.s1, S.s2);
+                    cache_key = key;
+                }
+            }
+            n2 = score_phase(smem, S, maps_of(g0, g1, g2, R.P), R.P, !WHOLE, cache.e01, cache.e23);
         }
         if (threadIdx.x == blockDim.x - 64)
             s_next[b] = next < total ? queue_item(q, 2LL * q.n + ticket, total) : total;
         __syncthreads();   // [C]
         const int after = __builtin_amdgcn_readfirstlane(s_next[b]);
         if (next < total) {
-            region_commit(smem, jobs[in.job], in.region, T);
+            region_commit<WHOLE>(smem, jobs[in.job], in.region, T);
             if (after < total) {
                 const fg_item ia = items[after];
-                region_prefetch(jobs[ia.job], ia.region, T);
+                region_prefetch<WHOLE>(jobs[ia.job], ia.region, T);
             }
         }
         // the previous region's slots, written by the threads the tile commit
@@ -2123,7 +2146,7 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
         // cleared after the next [A]
         if (have_prev && threadIdx.x >= QUAD_THREADS) {
             const fg_job &Jp = jobs[prev.job];
-            keys_write(Jp, item_region(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
+            keys_write(Jp, item_region<WHOLE>(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
                        threadIdx.x - QUAD_THREADS, blockDim.x - QUAD_THREADS);
         }
         if (full)
@@ -2141,9 +2164,37 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     __syncthreads();
     if (have_prev) {   // the last region used the buffer before the final flip of b
         const fg_job &Jp = jobs[prev.job];
-        keys_write(Jp, item_region(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)));
+        keys_write(Jp, item_region<WHOLE>(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)));
     }
     queue_exit(counter);
+}
+
+// For batches with whole regions.  What bounds it: vector issue two thirds of the
+// time (1295 vector instructions a wave and region) and, between the three
+// barriers, the latency of LDS and of the chains.  With whole regions' geometry
+// constant, the compass by byte averages and the sums in 16-bit lanes the 64-frame
+// batch went from 103 to 89 us.
+// Three waves a SIMD, which the LDS of three workgroups of 256 threads a CU allows
+// anyway: the constants of a whole region then stay in registers (at four waves,
+// 128 registers, 72 of them are spilled and the kernel takes 214 us instead of 90).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3, 3)))
+detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__ items, int total,
+                    unsigned *counter) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    batch_regions<true>(jobs, items, total, counter, smem);
+}
+
+// For batches with few whole regions or none.  Four waves a SIMD, 128 registers.
+// A region's columns in vector registers and its rows in scalar ones: 15 scalar
+// registers are spilled and no vector one; with both in vector ones 9 and 3.
+// 64 frames of one level and 32-pixel cells 85.6 us (95 while such regions shared
+// a kernel with whole ones, both coordinates in scalar registers), of two levels
+// 99.0 (108), of three levels and 48-pixel cells 138.2 (155.5).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
+detect_batch_any_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__ items, int total,
+                        unsigned *counter) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    batch_regions<false>(jobs, items, total, counter, smem);
 }
 
 // Generic persistent kernel: any region size and workgroup size, one region
@@ -2165,7 +2216,7 @@ __global__ void __launch_bounds__(512) detect_batch_generic_kernel(const fg_job 
         const int item = s_item;
         if (item >= total) break;
         const fg_item it = items[item];
-        detect_region(jobs[it.job], item_region(jobs[it.job], it.region), smem);
+        detect_region(jobs[it.job], item_region<true>(jobs[it.job], it.region), smem);
     }
     queue_exit(counter);
 }
@@ -2359,23 +2410,25 @@ hipError_t fg_launch_nms_grid(const fg_job &j, int radius, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int total, int total_upper,
-                           int max_levels, bool all_single, unsigned *counter, const fg_launch &L, hipStream_t s) {
+hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, const fg_batch_work &work, int total_upper,
+                           int max_levels, unsigned *counter, const fg_launch &L, hipStream_t s) {
     int blocks = L.num_cu * L.blocks_per_cu;
-    if (blocks > total) blocks = total;
+    if (blocks > work.total) blocks = work.total;
     if (blocks < 1) blocks = 1;
-    if (all_single && L.block >= 256)
-        hipLaunchKernelGGL(detect_batch_kernel, dim3(blocks), dim3(L.block), fg_smem_bytes(L.block), s,
-                           jobs_dev, items, total, counter);
-    else
-        hipLaunchKernelGGL(detect_batch_generic_kernel, dim3(blocks), dim3(L.block), fg_smem_bytes(L.block), s,
-                           jobs_dev, items, total, counter);
+    void (*kernel)(const fg_job *, const fg_item *, int, unsigned *) = detect_batch_generic_kernel;
+    switch (fg_choose_batch(work, L)) {
+        case fg_batch_kernel::WHOLE: kernel = detect_batch_kernel; break;
+        case fg_batch_kernel::ANY: kernel = detect_batch_any_kernel; break;
+        case fg_batch_kernel::GENERIC: break;
+    }
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(L.block), fg_smem_bytes(L.block), s, jobs_dev, items, work.total,
+                       counter);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || max_levels <= MAX_FUSED) return e;
     hipLaunchKernelGGL(upper_batch_kernel<3>, dim3(total_upper), dim3(L.block), fg_smem_bytes(L.block), s, jobs_dev,
-                       items + total);
+                       items + work.total);
     if (max_levels > 2 * MAX_FUSED)
         hipLaunchKernelGGL(upper_batch_kernel<6>, dim3(total_upper), dim3(L.block), fg_smem_bytes(L.block), s,
-                           jobs_dev, items + total);
+                           jobs_dev, items + work.total);
     return hipGetLastError();
 }

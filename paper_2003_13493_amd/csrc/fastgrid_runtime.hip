@@ -51,11 +51,11 @@ constexpr size_t items_offset(int njobs) { return (sizeof(fg_job) * (size_t)njob
 // The work items of a batch: one per region of every job, then one per upper
 // region of every job with more than FG_MAX_FUSED levels.
 struct Work {
-    int total = 0, total_upper = 0, max_levels = 1;
-    int limited = 0;          // what fast_submit_static's limit counts: regions, twice for jobs past 3 levels
-    bool all_single = true;   // every job's regions are single sub-tiles
+    fg_batch_work base{0, 0, true};
+    int total_upper = 0, max_levels = 1;
+    int limited = 0;   // what fast_submit_static's limit counts: regions, twice for jobs past 3 levels
 
-    int items() const { return total + total_upper; }   // at most `limited`
+    int items() const { return base.total + total_upper; }   // at most `limited`
 };
 
 struct Plan {
@@ -345,12 +345,13 @@ int build_table(fast_ctx *c, const fast_job *jobs, int njobs, fg_job *table, Wor
             return rc;
         }
         const fg_job &j = table[i];
-        table[i].region_base = work.total;
-        work.total += j.rx * j.ry;
+        table[i].region_base = work.base.total;
+        work.base.total += j.rx * j.ry;
+        work.base.whole += fg_whole_regions(j);
         work.limited += j.rx * j.ry * (q.levels > FG_MAX_FUSED ? 2 : 1);
         if (q.levels > FG_MAX_FUSED) work.total_upper += fg_upper_regions(j);
         if (q.levels > work.max_levels) work.max_levels = q.levels;
-        if (j.rcells * j.cell > FG_SUB) work.all_single = false;
+        if (j.rcells * j.cell > FG_SUB) work.base.all_single = false;
     }
     return FAST_OK;
 }
@@ -785,8 +786,7 @@ FG_API int fast_submit(fast_ctx *c, const fast_job *jobs, int njobs, void *strea
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = fg_launch_upload(S.dev, S.host, bytes, s);
     if (e != hipSuccess) return hip_fail(c, e, "job table upload");
-    e = fg_launch_batch(jobs_dev, items_dev, work.total, work.total_upper, work.max_levels,
-                        work.all_single, S.counter, c->launch, s);
+    e = fg_launch_batch(jobs_dev, items_dev, work.base, work.total_upper, work.max_levels, S.counter, c->launch, s);
     if (e != hipSuccess) return hip_fail(c, e, "batch launch");
     rc = record_ticket(c, s, ticket);
     if (rc) return rc;
@@ -830,7 +830,7 @@ FG_API int fast_submit_static(fast_ctx *c, const fast_job *jobs, int njobs, void
     if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord (static staging)");
     c->static_pending = true;
     e = fg_launch_batch((const fg_job *)(dev + STATIC_COUNTER_BYTES), (const fg_item *)(dev + off),
-                        work.total, work.total_upper, work.max_levels, work.all_single, (unsigned *)dev, c->launch, s);
+                        work.base, work.total_upper, work.max_levels, (unsigned *)dev, c->launch, s);
     if (e != hipSuccess) return hip_fail(c, e, "batch launch (static)");
     if (!ticket) return FAST_OK;
     return record_ticket(c, s, ticket);
@@ -1300,8 +1300,8 @@ FG_API int fast_plan_create(fast_ctx *c, const fast_job *jobs, int njobs, int fl
         if (!c->capture_stream) e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            hipError_t le = fg_launch_batch(p.dev, p.items, work.total, work.total_upper, work.max_levels,
-                                            work.all_single, p.counter, c->launch, c->capture_stream);
+            hipError_t le = fg_launch_batch(p.dev, p.items, work.base, work.total_upper, work.max_levels, p.counter,
+                                            c->launch, c->capture_stream);
             e = hipStreamEndCapture(c->capture_stream, &p.graph);
             if (le != hipSuccess) e = le;
         }
@@ -1330,8 +1330,8 @@ FG_API int fast_plan_launch(fast_ctx *c, int plan_id, void *stream, uint64_t *ti
     p.launched = true;
     p.last_stream = s;
     hipError_t e = p.exec ? hipGraphLaunch(p.exec, s)
-                          : fg_launch_batch(p.dev, p.items, p.work.total, p.work.total_upper, p.work.max_levels,
-                                            p.work.all_single, p.counter, c->launch, s);
+                          : fg_launch_batch(p.dev, p.items, p.work.base, p.work.total_upper, p.work.max_levels, p.counter,
+                                            c->launch, s);
     if (e != hipSuccess) return hip_fail(c, e, p.exec ? "hipGraphLaunch" : "plan launch");
     if (!ticket) return FAST_OK;
     return record_ticket(c, s, ticket);

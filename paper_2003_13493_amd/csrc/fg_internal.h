@@ -104,6 +104,9 @@ constexpr int FG_COUNTER_WORDS = FG_EXIT_WORD + FG_QUEUE_STRIDE;
 // (and XCDs) finishing up to 2% apart.
 constexpr int FG_QUEUE_RUN = 16;
 
+// Regions of at most this side (level-0 pixels) are one fused sub-tile.
+constexpr int FG_SUB = 64;
+
 // One work item of the batched kernels: a region of a job, its row << 16 | its
 // column (below 2^12 each), with FG_WHOLE set for a whole region of 64 x 64
 // pixels of a job of three levels and more.
@@ -116,6 +119,11 @@ constexpr uint32_t FG_WHOLE = 1u << 15;
 // Pyramid levels detected from one level-0 load; each FG_MAX_FUSED levels
 // further up take one more pass (levels 3-5, then 6-7).
 constexpr int FG_MAX_FUSED = 3;
+
+// Whole regions of a job (FG_WHOLE).
+__host__ __device__ constexpr int fg_whole_regions(const fg_job &j) {
+    return j.rcells * j.cell == FG_SUB && j.levels >= FG_MAX_FUSED ? (j.w[0] / FG_SUB) * (j.h[0] / FG_SUB) : 0;
+}
 
 // Cells per side of an upper region, the part of a frame one workgroup takes
 // in the passes over levels 3.. : 128 level-0 pixels (16 of level 3), at most
@@ -135,19 +143,37 @@ __host__ __device__ constexpr int fg_upper_regions(const fg_job &j) {
     return ((j.gw + c - 1) / c) * ((j.gh + c - 1) / c);
 }
 
+// The level-0 work of a batch: its regions, those that are whole, and whether
+// every job's regions are single 64x64 sub-tiles.
+struct fg_batch_work {
+    int total, whole;
+    bool all_single;
+};
+
+// The kernel that takes it.
+//   GENERIC  any region and workgroup size;
+//   ANY      regions that are single sub-tiles, workgroups of 256 threads and more;
+//   WHOLE    the same, with a path of its own for whole regions.
+// WHOLE takes a whole region in 0.88 of ANY's time and another one (of one or two
+// levels, or of cells that do not make 64 pixels) in 1.1 of it, so the line lies at
+// one whole region in four.  64 frames of three sizes, 16, 24, 32 and 40 of them of
+// three levels and the others of one: ANY 94.0, 96.2, 99.4 and 101.7 us, WHOLE 94.4,
+// 93.4, 93.9 and 93.7; the others of 48-pixel cells: ANY 132.2, 130.1, 125.8 and
+// 122.3, WHOLE 136.2, 130.7, 123.0 and 116.5.
+enum class fg_batch_kernel { GENERIC, ANY, WHOLE };
+constexpr fg_batch_kernel fg_choose_batch(const fg_batch_work &w, const fg_launch &L) {
+    if (!w.all_single || L.block < 256) return fg_batch_kernel::GENERIC;
+    return 4LL * w.whole >= w.total ? fg_batch_kernel::WHOLE : fg_batch_kernel::ANY;
+}
+
 // Copy `bytes` (a multiple of 8) of coherent pinned host memory to device
 // memory by a kernel on `s`.
 hipError_t fg_launch_upload(void *dev, const void *host, size_t bytes, hipStream_t s);
 
 // Batched path: `jobs_dev` is a device copy of the jobs, whose region_base
-// fields are prefix sums.  items[0 .. total) lists every region of every job
-// once, in any order; items[total .. total + total_upper) lists every upper
-// region of the jobs with more than FG_MAX_FUSED levels.
-// all_single: every job's regions are single 64x64 sub-tiles (the pipelined
-// kernel applies).  `counter` holds FG_COUNTER_WORDS zero-initialised words
+// fields are prefix sums.  items[0 .. work.total) lists every region of every job
+// once, in any order; the next total_upper items list every upper region of the
+// jobs with more than FG_MAX_FUSED levels.  `counter` holds FG_COUNTER_WORDS zero-initialised words
 // that the kernel re-arms itself on exit.
-hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, int total, int total_upper, int max_levels,
-                           bool all_single, unsigned *counter, const fg_launch &L, hipStream_t s);
-
-// Regions of at most this side (level-0 pixels) are one fused sub-tile.
-constexpr int FG_SUB = 64;
+hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, const fg_batch_work &work, int total_upper,
+                           int max_levels, unsigned *counter, const fg_launch &L, hipStream_t s);
