@@ -2169,7 +2169,8 @@ __device__ __forceinline__ void batch_regions(const fg_job *__restrict__ jobs, c
     queue_exit(counter);
 }
 
-// For batches with whole regions.  What bounds it: vector issue two thirds of the
+// For batches with whole regions, but not for several workgroups past 256 threads
+// a CU (fg_choose_batch).  What bounds it: vector issue two thirds of the
 // time (1295 vector instructions a wave and region) and, between the three
 // barriers, the latency of LDS and of the chains.  With whole regions' geometry
 // constant, the compass by byte averages and the sums in 16-bit lanes the 64-frame
@@ -2184,7 +2185,8 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
     batch_regions<true>(jobs, items, total, counter, smem);
 }
 
-// For batches with few whole regions or none.  Four waves a SIMD, 128 registers.
+// For batches with few whole regions or none, and for several workgroups past 256
+// threads a CU.  Four waves a SIMD, 128 registers.
 // A region's columns in vector registers and its rows in scalar ones: 15 scalar
 // registers are spilled and no vector one; with both in vector ones 9 and 3.
 // 64 frames of one level and 32-pixel cells 85.6 us (95 while such regions shared

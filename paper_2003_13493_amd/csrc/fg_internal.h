@@ -160,9 +160,16 @@ struct fg_batch_work {
 // three levels and the others of one: ANY 94.0, 96.2, 99.4 and 101.7 us, WHOLE 94.4,
 // 93.4, 93.9 and 93.7; the others of 48-pixel cells: ANY 132.2, 130.1, 125.8 and
 // 122.3, WHOLE 136.2, 130.7, 123.0 and 116.5.
+//
+// WHOLE has 168 registers, three waves a SIMD, so that of workgroups past 256
+// threads (two waves on a SIMD) one is resident where ANY's 128 registers let two
+// be.  64 frames of three levels with 320 threads and 3 workgroups a CU: WHOLE
+// 203 us, ANY 140; 384 and 2, 198 and 136; 512 and 2, 186 and 129; 512 and 1, 171
+// and 195.
 enum class fg_batch_kernel { GENERIC, ANY, WHOLE };
 constexpr fg_batch_kernel fg_choose_batch(const fg_batch_work &w, const fg_launch &L) {
     if (!w.all_single || L.block < 256) return fg_batch_kernel::GENERIC;
+    if (L.block > 256 && L.blocks_per_cu > 1) return fg_batch_kernel::ANY;
     return 4LL * w.whole >= w.total ? fg_batch_kernel::WHOLE : fg_batch_kernel::ANY;
 }
 

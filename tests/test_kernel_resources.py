@@ -47,3 +47,8 @@ def test_batches_without_whole_regions(kernels):
     k = one(kernels, "detect_batch_any_kernel")
     assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
     assert k["sgpr_spill_count"] <= 30
+
+
+def test_wide_workgroups(kernels):
+    """Two workgroups of 512 threads on a CU take 128 registers of a thread at most."""
+    assert one(kernels, "detect_batch_any_kernel")["vgpr_count"] <= 128
