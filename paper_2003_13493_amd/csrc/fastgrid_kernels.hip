@@ -2200,7 +2200,15 @@ detect_batch_any_kernel(const fg_job *__restrict__ jobs, const fg_item *__restri
 }
 
 // Generic persistent kernel: any region size and workgroup size, one region
-// at a time.
+// at a time.  Its general geometry, a hundred words the same in every lane, takes
+// the scalar registers or the vector ones:
+//   from the region's index by div_small, whose value lies in a vector register,
+//   157 registers and 60 scalar ones spilled;
+//   from the item's row and column, 112 registers, which let two workgroups past
+//   256 threads share a CU (WIDE), and 116 spilled.
+// 64 frames of three levels, 40-pixel cells, 256 threads 192.5 us by the index and
+// 209.2 by row and column; regions of 128 pixels, 512 threads and 2 a CU, 235 and 159.
+template <bool WIDE>
 __global__ void __launch_bounds__(512) detect_batch_generic_kernel(const fg_job *__restrict__ jobs,
                                                                    const fg_item *__restrict__ items,
                                                                    int total, unsigned *counter) {
@@ -2218,7 +2226,9 @@ __global__ void __launch_bounds__(512) detect_batch_generic_kernel(const fg_job 
         const int item = s_item;
         if (item >= total) break;
         const fg_item it = items[item];
-        detect_region(jobs[it.job], item_region<true>(jobs[it.job], it.region), smem);
+        const fg_job &J = jobs[it.job];
+        const int column = (int)(it.region & (FG_WHOLE - 1)), row = (int)(it.region >> 16);
+        detect_region(J, WIDE ? region_at(J, column, row) : region_of(J, row * J.rx + column), smem);
     }
     queue_exit(counter);
 }
@@ -2417,11 +2427,12 @@ hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, const f
     int blocks = L.num_cu * L.blocks_per_cu;
     if (blocks > work.total) blocks = work.total;
     if (blocks < 1) blocks = 1;
-    void (*kernel)(const fg_job *, const fg_item *, int, unsigned *) = detect_batch_generic_kernel;
+    void (*kernel)(const fg_job *, const fg_item *, int, unsigned *) = nullptr;
     switch (fg_choose_batch(work, L)) {
         case fg_batch_kernel::WHOLE: kernel = detect_batch_kernel; break;
         case fg_batch_kernel::ANY: kernel = detect_batch_any_kernel; break;
-        case fg_batch_kernel::GENERIC: break;
+        case fg_batch_kernel::GENERIC_WIDE: kernel = detect_batch_generic_kernel<true>; break;
+        case fg_batch_kernel::GENERIC: kernel = detect_batch_generic_kernel<false>; break;
     }
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(L.block), fg_smem_bytes(L.block), s, jobs_dev, items, work.total,
                        counter);

@@ -151,9 +151,11 @@ struct fg_batch_work {
 };
 
 // The kernel that takes it.
-//   GENERIC  any region and workgroup size;
-//   ANY      regions that are single sub-tiles, workgroups of 256 threads and more;
-//   WHOLE    the same, with a path of its own for whole regions.
+//   GENERIC       any region and workgroup size;
+//   GENERIC_WIDE  the same with at most 128 registers;
+//   ANY           regions that are single sub-tiles, workgroups of 256 threads and
+//                 more, at most 128 registers;
+//   WHOLE         the same with 168 and a path of its own for whole regions.
 // WHOLE takes a whole region in 0.88 of ANY's time and another one (of one or two
 // levels, or of cells that do not make 64 pixels) in 1.1 of it, so the line lies at
 // one whole region in four.  64 frames of three sizes, 16, 24, 32 and 40 of them of
@@ -161,16 +163,15 @@ struct fg_batch_work {
 // 93.4, 93.9 and 93.7; the others of 48-pixel cells: ANY 132.2, 130.1, 125.8 and
 // 122.3, WHOLE 136.2, 130.7, 123.0 and 116.5.
 //
-// WHOLE has 168 registers, three waves a SIMD, so that of workgroups past 256
-// threads (two waves on a SIMD) one is resident where ANY's 128 registers let two
-// be.  64 frames of three levels with 320 threads and 3 workgroups a CU: WHOLE
+// With more than 128 registers, three waves a SIMD, one workgroup past 256 threads
+// (two waves on a SIMD) is resident where 128 let two be.  64 frames of three levels with 320 threads and 3 workgroups a CU: WHOLE
 // 203 us, ANY 140; 384 and 2, 198 and 136; 512 and 2, 186 and 129; 512 and 1, 171
 // and 195.
-enum class fg_batch_kernel { GENERIC, ANY, WHOLE };
+enum class fg_batch_kernel { GENERIC, GENERIC_WIDE, ANY, WHOLE };
 constexpr fg_batch_kernel fg_choose_batch(const fg_batch_work &w, const fg_launch &L) {
-    if (!w.all_single || L.block < 256) return fg_batch_kernel::GENERIC;
-    if (L.block > 256 && L.blocks_per_cu > 1) return fg_batch_kernel::ANY;
-    return 4LL * w.whole >= w.total ? fg_batch_kernel::WHOLE : fg_batch_kernel::ANY;
+    const bool wide = L.block > 256 && L.blocks_per_cu > 1;
+    if (!w.all_single || L.block < 256) return wide ? fg_batch_kernel::GENERIC_WIDE : fg_batch_kernel::GENERIC;
+    return !wide && 4LL * w.whole >= w.total ? fg_batch_kernel::WHOLE : fg_batch_kernel::ANY;
 }
 
 // Copy `bytes` (a multiple of 8) of coherent pinned host memory to device

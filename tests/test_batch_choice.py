@@ -6,13 +6,14 @@ import pytest
 
 from paper_2003_13493_amd import build
 
-GENERIC, ANY, WHOLE = range(3)
+GENERIC, GENERIC_WIDE, ANY, WHOLE = range(4)
 
 # total, whole, single sub-tiles, threads, workgroups a CU, kernel
 CASES = [(96, 77, 1, 256, 3, WHOLE), (96, 24, 1, 256, 3, WHOLE), (96, 23, 1, 256, 3, ANY), (97, 24, 1, 256, 3, ANY),
          (96, 0, 1, 256, 3, ANY), (1, 0, 1, 256, 1, ANY), (1, 1, 1, 256, 16, WHOLE),
          (96, 77, 1, 256, 4, WHOLE), (96, 77, 1, 320, 3, ANY), (96, 77, 1, 384, 2, ANY), (96, 77, 1, 448, 2, ANY),
          (96, 77, 1, 512, 2, ANY), (96, 77, 1, 512, 1, WHOLE), (96, 77, 1, 320, 1, WHOLE), (96, 0, 1, 512, 1, ANY),
+         (96, 77, 0, 320, 2, GENERIC_WIDE), (96, 0, 0, 512, 16, GENERIC_WIDE), (96, 77, 0, 512, 1, GENERIC),
          (96, 77, 0, 256, 3, GENERIC), (96, 77, 1, 192, 3, GENERIC), (96, 0, 1, 64, 6, GENERIC),
          (1 << 30, 1 << 29, 1, 256, 3, WHOLE), (1 << 30, 1 << 27, 1, 256, 3, ANY)]
 

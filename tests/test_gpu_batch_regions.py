@@ -47,7 +47,8 @@ def frames_of(mix):
     return [out[k] for k in order]
 
 
-@pytest.mark.parametrize("shape", [(64, 256, 3), (64, 256, 1), (32, 256, 2), (64, 320, 1), (64, 384, 2), (64, 512, 2)], ids=lambda s: "%d_%d_%d" % s)
+@pytest.mark.parametrize("shape", [(64, 256, 3), (64, 256, 1), (32, 256, 2), (64, 320, 1), (64, 384, 2), (64, 512, 2),
+                                   (128, 256, 1), (128, 512, 2), (256, 320, 2), (256, 128, 4)], ids=lambda s: "%d_%d_%d" % s)
 @pytest.mark.parametrize("mix", list(MIXES))
 def test_batch(ctx, mix, shape):
     print(f"case batch regions {mix} {shape}", flush=True)

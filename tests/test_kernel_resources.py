@@ -51,4 +51,12 @@ def test_batches_without_whole_regions(kernels):
 
 def test_wide_workgroups(kernels):
     """Two workgroups of 512 threads on a CU take 128 registers of a thread at most."""
-    assert one(kernels, "detect_batch_any_kernel")["vgpr_count"] <= 128
+    for name in ("detect_batch_any_kernel", "detect_batch_generic_kernelILb1E"):
+        assert one(kernels, name)["vgpr_count"] <= 128
+
+
+def test_generic_batches(kernels):
+    """The general geometry of regions of any size stays clear of the scalar registers."""
+    k = one(kernels, "detect_batch_generic_kernelILb0E")
+    assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
+    assert k["sgpr_spill_count"] <= 80
