@@ -893,14 +893,14 @@ __device__ __forceinline__ void store_maps(const uint8_t *smem, const Geo &g0, c
 
 // Detect levels g0..g(nl-1) of the staged sub-tile (score maps zeroed) and fold
 // the survivors into the region's cell keys, or write its scores to the global
-// maps (P.smap).  One barrier makes all scores visible before NMS.  `cache`
-// (workgroups of four or more waves only): the group entries, filled by the
-// caller.
+// maps (P.smap).  One barrier makes all scores visible before NMS.  With `cached`
+// (workgroups of four or more waves only) `cache` holds the group entries, filled
+// by the caller; a value, since a pointer that may be null keeps it in memory.
 __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Geo &g2, int nl, const Params &P,
-                           uint32_t *keys, const GroupCache *cache = nullptr) {
+                           uint32_t *keys, bool cached = false, GroupCache cache = GroupCache{0u, 0u}) {
     const Segs S = segs_of(g0, g1, g2, nl);
     const Maps M = maps_of(g0, g1, g2, P);
-    const int n2 = score_phase(smem, S, M, P, cache != nullptr, cache ? cache->e01 : 0u, cache ? cache->e23 : 0u);
+    const int n2 = score_phase(smem, S, M, P, cached, cache.e01, cache.e23);
     __syncthreads();   // every level's scores, ring included, are in the maps
     if (P.smap[0]) {   // score-map mode
         store_maps(smem, g0, g1, g2, nl, P);
@@ -1539,7 +1539,7 @@ __device__ __forceinline__ void upper_region(const fg_job &J, int rxi, int ryi, 
     // while the first rows load: the maps, the slots so far, the compass groups
     zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
     if (!SCORES) keys_from_slots(J, R, keys);
-    GroupCache cache;
+    GroupCache cache{0u, 0u};
     const bool cached = blockDim.x >= 256;
     if (cached) group_cache_fill(cache, g0, g1, g2, F);
     for (int i = threadIdx.x;;) {
@@ -1561,7 +1561,7 @@ __device__ __forceinline__ void upper_region(const fg_job &J, int rxi, int ryi, 
             R.P.smap[l] = J.smap[B + l];
             R.P.spitch[l] = J.smap_pitch[B + l];
         }
-    run_passes(smem, g0, g1, g2, F, R.P, keys, cached ? &cache : nullptr);
+    run_passes(smem, g0, g1, g2, F, R.P, keys, cached, cache);
     if (SCORES) return;
     __syncthreads();
     keys_write(J, R, keys);
@@ -1928,7 +1928,7 @@ __device__ __forceinline__ void single_region(const fg_job &J, uint8_t *smem) {
     if (ch < (st.tw >> 4) && 4 * q < st.th) quad_commit(smem, T, q, ch, st, J, 0, nl, g1, g2);
     __syncthreads();
     if (!full) {
-        run_passes(smem, g0, g1, g2, nl, R.P, keys, &cache);
+        run_passes(smem, g0, g1, g2, nl, R.P, keys, true, cache);
     } else {
         const int n2 = score_phase(smem, WR::segs(R.P.rx0, R.P.ry0, J.w[0], J.h[0]), WR::maps(J.cell), R.P, true,
                                    cache.e01, cache.e23);

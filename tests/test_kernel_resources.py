@@ -60,3 +60,8 @@ def test_generic_batches(kernels):
     k = one(kernels, "detect_batch_generic_kernelILb0E")
     assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
     assert k["sgpr_spill_count"] <= 80
+
+
+def test_nothing_in_scratch_memory(kernels):
+    """No kernel keeps a value in private memory, by a spill or by an address taken."""
+    assert {k: v for k, v in kernels.items() if v["private_segment_fixed_size"] or v["vgpr_spill_count"]} == {}
