@@ -53,9 +53,8 @@ def build_synth(verbose: bool = False) -> str:
     return out
 
 
-def build_fastgrid(verbose: bool = False, extra: list[str] | None = None) -> str:
-    out = os.path.join(HERE, "libfastgrid.so")
-    srcs = [os.path.join(CSRC, s) for s in HIP_SOURCES]
+def build_hip(out: str, srcs: list[str], verbose: bool = False, extra: list[str] | None = None) -> str:
+    """One shared object from HIP sources, with the library's own flags."""
     cmd = [_hipcc(), *HIPCC_FLAGS, "-I", INCLUDE, "-I", CSRC, *(extra or []),
            "-o", out + ".tmp", *srcs]
     if verbose:
@@ -63,6 +62,11 @@ def build_fastgrid(verbose: bool = False, extra: list[str] | None = None) -> str
     subprocess.run(cmd, check=True)
     os.replace(out + ".tmp", out)
     return out
+
+
+def build_fastgrid(verbose: bool = False, extra: list[str] | None = None) -> str:
+    return build_hip(os.path.join(HERE, "libfastgrid.so"), [os.path.join(CSRC, s) for s in HIP_SOURCES],
+                     verbose, extra)
 
 
 def build_all(verbose: bool = False) -> None:

@@ -146,7 +146,9 @@ __device__ __forceinline__ uint32_t load_at(const uint8_t *base, uint32_t offset
 // The correctly rounded square root and reciprocal of x in [2^-98, 2^120] by
 // Newton steps with fused residuals (Markstein's method), 8 and 3 instructions
 // where the compiler's, which also take zeros, infinities and subnormals, are 16
-// and 10.  Equal to those for every mantissa at every exponent of that range.
+// and 10.  That they are correctly rounded is no property of the steps alone, which
+// from some starting values miss by an ulp, but of the steps and gfx950's v_rsq_f32
+// and v_rcp_f32: tests/test_gpu_rounding.py compares all mantissas.
 __device__ __forceinline__ float sqrt_rounded(float x) {
     const float y = __builtin_amdgcn_rsqf(x);
     const float g = x * y, h = 0.5f * y, r = __builtin_fmaf(-h, g, 0.5f);
