@@ -42,8 +42,8 @@ constexpr int SUB = FG_SUB;             // sub-tile side at level 0
 constexpr int MAX_FUSED = FG_MAX_FUSED;   // levels built in LDS from one load
 
 // All level tiles share one LDS row pitch, so circle offsets are constants.
-// Band A (rows 0..95): level 0 of a fused sub-tile, or the current level of an
-// unfused one.  Band B (rows 96..143): level 1 at byte 8, level 2 at byte 68.
+// Band A (rows 0..95): level 0 of a fused sub-tile, or the first level of an upper
+// region.  Band B (rows 96..143): the next level at byte 8, the one after at byte 68.
 // For a sub-tile whose origin is a multiple of 16 pixels, the compass groups
 // of every level then start 4 bytes past a multiple of 8, so the row words
 // around a group are two aligned 8-byte reads (load8<true>).
@@ -57,10 +57,8 @@ static_assert(T1 % 8 == 0 && T2 % 4 == 0, "8-byte reads when halving level 1");
 static_assert(LP % 8 == 0 && T0 % 8 == 0 && T1 % 8 == 0 && T2 % 8 == 4, "aligned compass row reads");
 static_assert(TILE_BYTES <= 16384, "entries hold 14-bit LDS offsets");
 // Score maps: a level's sub-tile area plus a 1-pixel ring.
-constexpr int M0_ROWS = SUB + 2, M0_P = SUB + 4;
-constexpr int M1_ROWS = SUB / 2 + 2, M1_P = M0_P;
-constexpr int M2_ROWS = SUB / 4 + 2, M2_P = M0_P;
-constexpr int MP = M0_P;   // one pitch for every level's score map
+constexpr int M0_ROWS = SUB + 2, M1_ROWS = SUB / 2 + 2, M2_ROWS = SUB / 4 + 2;
+constexpr int MP = SUB + 4;   // one pitch for every level's score map
 constexpr int MAX_RCELLS = 16;
 constexpr int MAX_KEYS = MAX_RCELLS * MAX_RCELLS;
 // Groups of 8 pixels scored per sub-tile, at most: every level's area plus a
@@ -116,15 +114,8 @@ __device__ __forceinline__ void gstore(void *p, T v) {
     *(GLOBAL T *)p = v;
 }
 
-__device__ __forceinline__ s16x2 as_s16x2(uint32_t v) { return __builtin_bit_cast(s16x2, v); }
-__device__ __forceinline__ uint32_t as_u32(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ __forceinline__ s16x2 vmax(s16x2 a, s16x2 b) { return __builtin_elementwise_max(a, b); }
 __device__ __forceinline__ s16x2 vmin(s16x2 a, s16x2 b) { return __builtin_elementwise_min(a, b); }
-
-// Two bytes of the 8-byte value {hi, lo} zero-extended into 16-bit lanes.
-__device__ __forceinline__ s16x2 pair(uint32_t hi, uint32_t lo, uint32_t sel) {
-    return as_s16x2(__builtin_amdgcn_perm(hi, lo, sel));
-}
 
 // floor(a / b) for 0 <= a < 2^21 and b >= 1 with the approximate reciprocal:
 // (a + 0.5) / b lies at least 0.5 / b from an integer, and the relative error
@@ -690,7 +681,7 @@ __device__ __forceinline__ void tile_rc(uint32_t off, int &row, int &col) {
 
 // Per-level constants for mapping an entry to its score map and cell.
 struct LevelMap {
-    int mp, mbias;       // map index = row * mp + col + mbias (row, col in the tile band)
+    int mbias;           // map index = row * MP + col + mbias (row, col in the tile band)
     int rlo, rhi;        // band rows of the sub-tile area: [rlo, rhi)
     int clo, chi;        // band columns of the sub-tile area: [clo, chi)
     int xo, yo;          // cell-relative position = (col + xo, row + yo)
@@ -702,7 +693,6 @@ __device__ __forceinline__ LevelMap level_map(const Geo &g, int band_row, int ba
                                              int rb, const Params &P) {
     LevelMap m;
     const int ybias = g.ty - band_row, xbias = g.tx - band_col;   // level y = row + ybias
-    m.mp = g.mp;
     m.mbias = (g.moff >> 1) + (ybias - (g.sy - 1)) * g.mp + (xbias - (g.sx - 1));
     m.rlo = ra - ybias;
     m.rhi = rb - ybias;
@@ -967,7 +957,6 @@ struct Whole {
         const Geo g = geo(l);
         const int row0 = l == 0 ? 0 : 96, col0 = g.tbase - row0 * LP;   // the tile's corner in its band
         LevelMap m;
-        m.mp = MP;
         m.mbias = (g.moff >> 1) + (1 - g.sy - row0) * MP + 1 - g.sx - col0;
         m.rlo = g.sy + row0;
         m.rhi = g.ey + row0;
@@ -1153,7 +1142,7 @@ __device__ void describe_fused(const fg_job &J, int sx0, int sy0, int xr1, int y
     g0.tx = st.tx;
     g0.ty = st.ty;
     g0.moff = OFF_M0;
-    g0.mp = M0_P;
+    g0.mp = MP;
     set_groups(g0);
     g1 = g0;
     g2 = g0;
@@ -1164,7 +1153,7 @@ __device__ void describe_fused(const fg_job &J, int sx0, int sy0, int xr1, int y
         g1.tx = st.tx >> 1;
         g1.ty = st.ty >> 1;
         g1.moff = OFF_M1;
-        g1.mp = M1_P;
+        g1.mp = MP;
         set_groups(g1);
     }
     if (nl > 2) {
@@ -1173,7 +1162,7 @@ __device__ void describe_fused(const fg_job &J, int sx0, int sy0, int xr1, int y
         g2.tx = st.tx >> 2;
         g2.ty = st.ty >> 2;
         g2.moff = OFF_M2;
-        g2.mp = M2_P;
+        g2.mp = MP;
         set_groups(g2);
     }
 }

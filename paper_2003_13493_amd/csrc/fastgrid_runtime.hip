@@ -65,7 +65,6 @@ struct Plan {
     unsigned *counter = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    int njobs = 0;
     Work work;
     bool launched = false;
     hipStream_t last_stream = nullptr;   // launches of a plan are ordered on one stream
@@ -345,7 +344,6 @@ int build_table(fast_ctx *c, const fast_job *jobs, int njobs, fg_job *table, Wor
             return rc;
         }
         const fg_job &j = table[i];
-        table[i].region_base = work.base.total;
         work.base.total += j.rx * j.ry;
         work.base.whole += fg_whole_regions(j);
         work.limited += j.rx * j.ry * (q.levels > FG_MAX_FUSED ? 2 : 1);
@@ -1278,7 +1276,6 @@ FG_API int fast_plan_create(fast_ctx *c, const fast_job *jobs, int njobs, int fl
     DeviceGuard g(c->device);
     reap(c, false);   // a setup call: release what destroyed plans left behind
     Plan p;
-    p.njobs = njobs;
     p.work = work;
     std::vector<fg_item> items((size_t)work.items());
     fill_items(table.data(), njobs, items.data());

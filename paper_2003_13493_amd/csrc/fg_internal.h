@@ -21,7 +21,6 @@ struct fg_job {
     int32_t gw, gh;                  // grid size in cells
     int32_t rcells;                  // cells per region side
     int32_t rx, ry;                  // regions across, down
-    int32_t region_base;             // first work item of this job in a batch
 };
 
 // Launch shape knobs (set per context by fast_set_launch / the autotuner).
@@ -178,10 +177,10 @@ constexpr fg_batch_kernel fg_choose_batch(const fg_batch_work &w, const fg_launc
 // memory by a kernel on `s`.
 hipError_t fg_launch_upload(void *dev, const void *host, size_t bytes, hipStream_t s);
 
-// Batched path: `jobs_dev` is a device copy of the jobs, whose region_base
-// fields are prefix sums.  items[0 .. work.total) lists every region of every job
-// once, in any order; the next total_upper items list every upper region of the
-// jobs with more than FG_MAX_FUSED levels.  `counter` holds FG_COUNTER_WORDS zero-initialised words
-// that the kernel re-arms itself on exit.
+// Batched path: `jobs_dev` is a device copy of the jobs.  items[0 .. work.total)
+// lists every region of every job once, in any order; the next total_upper items
+// list every upper region of the jobs with more than FG_MAX_FUSED levels.
+// `counter` holds FG_COUNTER_WORDS zero-initialised words that the kernel re-arms
+// itself on exit.
 hipError_t fg_launch_batch(const fg_job *jobs_dev, const fg_item *items, const fg_batch_work &work, int total_upper,
                            int max_levels, unsigned *counter, const fg_launch &L, hipStream_t s);
