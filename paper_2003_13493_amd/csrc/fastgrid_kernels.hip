@@ -1240,12 +1240,17 @@ __device__ __forceinline__ Region region_at(const fg_job &J, int rxi, int ryi, b
     return R;
 }
 
-// The region of an item, its column (and with VROW its row) in a vector register,
-// and with it what follows from it: of the general set-up's hundred words that
-// are the same in every lane, more are spilled and reloaded lane by lane in the
-// passes when all compete for the scalar registers.
-template <bool VROW>
 __device__ __forceinline__ Region item_region(const fg_job &J, uint32_t code) {
+    return region_at(J, (int)(code & (FG_WHOLE - 1)), (int)(code >> 16));
+}
+// The region of an item for the general passes, its column (and with VROW its row)
+// in a vector register, and with it what follows from it: of the general set-up's
+// hundred words that are the same in every lane, more are spilled and reloaded lane
+// by lane in the passes when all compete for the scalar registers.  Tile loads and
+// commits take item_region: vector coordinates lengthen their chains (16 frames of
+// 752x480, SAD-A, N = 12: 26.2 us, 27.0 with them there too).
+template <bool VROW>
+__device__ __forceinline__ Region general_region(const fg_job &J, uint32_t code) {
     int column = (int)(code & (FG_WHOLE - 1)), row = (int)(code >> 16);
     asm("" : "+v"(column));
     if (VROW) asm("" : "+v"(row));
@@ -1597,7 +1602,7 @@ __device__ __forceinline__ void region_prefetch(const fg_job &J, uint32_t code, 
     if (WHOLE && (code & FG_WHOLE)) {
         quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], whole_stage(whole_region(J, code)));
     } else {
-        const Region R = item_region<WHOLE>(J, code);
+        const Region R = item_region(J, code);
         quad_issue(T, J.lvl[0], J.h[0], J.pitch[0], fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1));
     }
 }
@@ -1609,7 +1614,7 @@ __device__ __forceinline__ void region_commit(uint8_t *smem, const fg_job &J, ui
         whole_commit(smem, T, J, whole_region(J, code));
         return;
     }
-    const Region R = item_region<WHOLE>(J, code);
+    const Region R = item_region(J, code);
     const Stage st = fused_stage(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1);
     Geo g0, g1, g2;
     describe_fused(J, R.P.rx0, R.P.ry0, R.xr1, R.yr1, st, g0, g1, g2);
@@ -2079,10 +2084,13 @@ __device__ __forceinline__ void batch_regions(const fg_job *__restrict__ jobs, c
     GroupCache cache{0u, 0u};   // with WHOLE, the whole regions' entries; without, those of geometry cache_key
     if (WHOLE) W3::fill(cache);
     int cache_key = -1;
+    auto slots_region = [](const fg_job &J, uint32_t code) {
+        return WHOLE && (code & FG_WHOLE) ? whole_region(J, code) : general_region<WHOLE>(J, code);
+    };
     while (item < total) {
         const fg_job &J = jobs[il.job];   // uniform: read through the scalar cache
         const bool full = WHOLE && (il.region & FG_WHOLE);
-        const Region R = full ? whole_region(J, il.region) : item_region<WHOLE>(J, il.region);
+        const Region R = full ? whole_region(J, il.region) : general_region<WHOLE>(J, il.region);
         uint32_t *keys = (uint32_t *)(smem + (b ? OFF_KEYS2 : OFF_KEYS));
         __syncthreads();   // [A]
         zero_lds(smem + OFF_M0, OFF_KEYS - OFF_M0);
@@ -2135,7 +2143,7 @@ __device__ __forceinline__ void batch_regions(const fg_job *__restrict__ jobs, c
         // cleared after the next [A]
         if (have_prev && threadIdx.x >= QUAD_THREADS) {
             const fg_job &Jp = jobs[prev.job];
-            keys_write(Jp, item_region<WHOLE>(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
+            keys_write(Jp, slots_region(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)),
                        threadIdx.x - QUAD_THREADS, blockDim.x - QUAD_THREADS);
         }
         if (full)
@@ -2153,7 +2161,7 @@ __device__ __forceinline__ void batch_regions(const fg_job *__restrict__ jobs, c
     __syncthreads();
     if (have_prev) {   // the last region used the buffer before the final flip of b
         const fg_job &Jp = jobs[prev.job];
-        keys_write(Jp, item_region<WHOLE>(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)));
+        keys_write(Jp, slots_region(Jp, prev.region), (const uint32_t *)(smem + (b ? OFF_KEYS : OFF_KEYS2)));
     }
     queue_exit(counter);
 }
