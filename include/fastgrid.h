@@ -246,7 +246,7 @@ int fast_track(fast_ctx *ctx, const fast_plane *tpl, const fast_plane *img, int 
  * fast_detect_grid_score, which also builds the current pyramid's levels),
  * on the same stream.  The paper's evaluation detects with SAD-A.
  * tracking parameters (mode, max_iter, eps) are as for fast_track and shared
- * by all jobs.  Asynchronous on `stream`; the job table travels in one copy
+ * by all jobs.  Asynchronous on `stream`; the job table travels in one upload
  * from a context staging slot, like fast_submit (FAST_EBUSY when all are in
  * flight); *ticket (may be NULL) works as for fast_submit.
  * Errors: FAST_EINVAL for NULL jobs, njobs not in 1..FAST_MAX_JOBS, bad
@@ -277,8 +277,9 @@ int fast_frontend_step(fast_ctx *ctx, const fast_frontend_job *jobs, int njobs, 
 
 /* Batched path: all `njobs` requests (1..FAST_MAX_JOBS, any mix of sizes and
  * parameters) run in one persistent launch fed by a device-side work queue.
- * The job table and its work-item list are enqueued on `stream` as one copy
- * from library-owned pinned memory, followed by the kernels; nothing blocks.
+ * The job table and its work-item list are enqueued on `stream` as one upload (a
+ * small kernel that reads library-owned pinned memory), followed by the kernels;
+ * nothing blocks.
  * *ticket identifies the submission for fast_poll / fast_wait.
  * Each job is validated like fast_detect_grid; one bad job rejects the whole
  * submission with FAST_EINVAL and nothing is enqueued.  FAST_EBUSY if the

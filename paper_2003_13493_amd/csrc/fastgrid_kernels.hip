@@ -8,7 +8,8 @@
 // loaded once with a 4*2^(L-1)-pixel halo for its first L <= 3 levels, and levels
 // 1 and 2 are built from it in LDS (one pass over HBM: level 0 read once, levels
 // 1.. written once).  Levels 3.. follow in one more pass per three levels, by
-// regions of 128 pixels of the level below, which build and detect theirs alike.
+// regions of 128 level-0 pixels (16 of level 3), which build and detect theirs
+// alike.
 //
 // Detection of a sub-tile scores every pixel of its area plus a 1-pixel ring
 // at every level:
@@ -903,8 +904,9 @@ __device__ void run_passes(uint8_t *smem, const Geo &g0, const Geo &g1, const Ge
 // regions of a frame are: everything but the testable columns and rows (the
 // region may lie at the frame's edge) and the cell side is a constant, which
 // takes the set-up of the general case, and the scalar registers that hold it,
-// off every region's path.  With it a region of the 64-frame batch takes 390
-// scalar instructions a wave instead of 660 (98.6 -> 90.0 us).
+// off every region's path.  With it, and with items that name a region by its
+// place, a region of the 64-frame batch takes 456 scalar instructions a wave where
+// it took about 930 (98.6 -> 86.6 us when both came).
 // (rx0, ry0): the region's origin; W, H: level 0.
 template <int SIDE, int NL>
 struct Whole {
@@ -2167,11 +2169,12 @@ __device__ __forceinline__ void batch_regions(const fg_job *__restrict__ jobs, c
 }
 
 // For batches with whole regions, but not for several workgroups past 256 threads
-// a CU (fg_choose_batch).  What bounds it: vector issue two thirds of the
-// time (1295 vector instructions a wave and region) and, between the three
-// barriers, the latency of LDS and of the chains.  With whole regions' geometry
-// constant, the compass by byte averages and the sums in 16-bit lanes the 64-frame
-// batch went from 103 to 89 us.
+// a CU (fg_choose_batch).  What bounds it: vector issue 60% of the time (1324
+// vector instructions a wave and region) and, between the three barriers, the
+// latency of LDS and of the chains.  With whole regions' geometry constant, the
+// compass by byte averages and the sums in 16-bit lanes the 64-frame batch went
+// from 103 to 89.7 us, with clipped regions' coordinates in vector registers (54
+// scalar registers spilled instead of 94) to 87.7.
 // Three waves a SIMD, which the LDS of three workgroups of 256 threads a CU allows
 // anyway: the constants of a whole region then stay in registers (at four waves,
 // 128 registers, 72 of them are spilled and the kernel takes 214 us instead of 90).
@@ -2386,7 +2389,9 @@ static bool single_regions(const fg_job &j, const fg_launch &L) { return j.rcell
 
 // The kernel whose whole regions (Whole) are the frame's: 64 or 32 pixels a
 // side, which the default rule gives, three levels and more or one.  Regions of
-// another side or of two levels take the general set-up in it (1 to 3% slower).
+// another side or of two levels take the general set-up in it: 1920x1080 with two
+// levels 12.0 us (12.8 in detect_plain_kernel, which they took before), with three
+// and 48-pixel cells 14.3 (15.8), 640x480 with two 7.4 (8.0).
 template <int SIDE>
 static void (*single_kernel(int levels, bool scores))(fg_job) {
     if (levels == 1) return scores ? score_single_kernel<SIDE, 1> : detect_single_kernel<SIDE, 1>;

@@ -30,8 +30,8 @@ constexpr int TABLE_SLOTS = 8;     // job tables that may be in flight at once
 constexpr int DEFAULT_REGION = 64;
 constexpr int SMALL_REGION = 32;
 
-// A submission's job table and work items travel in one host-to-device copy:
-// the jobs at offset 0 and the items from items_offset(njobs), in a pinned
+// A submission's job table and work items travel in one upload
+// (fg_launch_upload): the jobs at offset 0 and the items from items_offset(njobs), in a pinned
 // staging buffer and its device twin of `cap` bytes.
 struct TableSlot {
     uint8_t *host = nullptr;       // pinned staging buffer
@@ -160,9 +160,12 @@ int fail(fast_ctx *c, int code, const std::string &msg) {
 // != 0) that side; else the tuned side of the frame's shape, if the shape
 // table has one; otherwise the batch side, unless the frame has fewer
 // regions than half the CUs and at most 3 levels: then 32-pixel regions give
-// 4x the workgroups at a still moderate halo cost (MI355X, 256 threads:
-// 640x480 L=3 10.8 us against 17.7 us; 1280x720, 240 regions, 16.6 against
-// 15.0 us; 1920x1080 L=4 42.5 against 24.5 us).
+// 4x the workgroups at a still moderate halo cost (MI355X, 256 threads, 32-pixel
+// cells: 640x480 L=3 8.0 us against 10.9; 1280x720, 240 regions, 11.2 against
+// 10.4; 1920x1080 L=4 26.7 against 20.2).  Frames of 4 and 5 levels that small
+// would gain too (640x480 15.9 against 18.7 and 16.7 against 19.6); the limit of 3
+// dates from when each deeper level was a launch over level-0 regions, and the
+// shape table can give such a frame 32.
 void plain_layout(const fast_ctx *c, fg_job &j) {
     fg_launch L = c->launch;
     if (L.plain_region) {

@@ -131,7 +131,10 @@ __host__ __device__ constexpr int fg_whole_regions(const fg_job &j) {
 // frame: 1920x1080, 4 levels, 7.9 us with 128 (135 workgroups) and 9.0 with
 // 256 (40 of 256 CUs busy); 4096x2160, 5 levels, 10.3 us with 128 and 9.4 with
 // 256; 64 or fewer spend a workgroup's whole chain of loads and passes on 64
-// pixels of level 3 (27 us for that frame's 2176 regions).
+// pixels of level 3 (27 us for that frame's 2176 regions).  The pass over levels 6
+// and 7 takes the same regions, 2 pixels of level 6 a side: up to 4096x2160 its
+// workgroups (544) are all resident at once, so it lasts one chain (6 to 7 us)
+// whatever their size.
 constexpr int FG_UPPER_SIDE = 128;
 __host__ __device__ constexpr int fg_upper_cells(int cell, int rcells) {
     const int c = FG_UPPER_SIDE / cell;
