@@ -2189,9 +2189,9 @@ detect_batch_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__
 // threads a CU.  Four waves a SIMD, 128 registers.
 // A region's columns in vector registers and its rows in scalar ones: 15 scalar
 // registers are spilled and no vector one; with both in vector ones 9 and 3.
-// 64 frames of one level and 32-pixel cells 85.6 us (95 while such regions shared
+// 64 frames of one level and 32-pixel cells 85.7 us (95.3 while such regions shared
 // a kernel with whole ones, both coordinates in scalar registers), of two levels
-// 99.0 (108), of three levels and 48-pixel cells 138.2 (155.5).
+// 97.9 (107.6), of three levels and 48-pixel cells 137.1 (155.4).
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 detect_batch_any_kernel(const fg_job *__restrict__ jobs, const fg_item *__restrict__ items, int total,
                         unsigned *counter) {

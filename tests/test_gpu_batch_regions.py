@@ -67,3 +67,26 @@ def test_batch(ctx, mix, shape):
                     assert np.array_equal(p.level(k), planes[k][0][:, :planes[k][1]]), f"{tag} level {k}"
     finally:
         ctx.reset_launch()
+
+
+@pytest.mark.parametrize("graph", [False, True], ids=["direct", "graph"])
+def test_plan_under_other_shapes(ctx, graph):
+    """A resident batch keeps its regions; the workgroups that a launch uses, and
+    with them the kernel, follow the context's shape of the moment (a captured
+    launch keeps its own)."""
+    print(f"case batch regions plan graph={graph}", flush=True)
+    frames = frames_of("most")
+    jobs = ctx.make_jobs((p, 12, 9, cell, g) for p, g, cell, _, _ in frames)
+    pid = ctx.plan_create(jobs, graph=graph)
+    try:
+        for shape in [(0, 256, 3), (0, 512, 2), (0, 128, 4), (0, 512, 1), (0, 320, 2), (0, 256, 1)]:
+            ctx.set_launch(*shape)
+            for _, g, _, _, _ in frames:
+                g.tensor.fill_(0x5A)
+            ctx.plan_launch(pid, ticket=False)
+            torch.cuda.synchronize()
+            for i, (_, g, _, want, _) in enumerate(frames):
+                assert np.array_equal(g.fetch(), want), f"{shape} frame {i}"
+    finally:
+        ctx.plan_destroy(pid)
+        ctx.reset_launch()
